@@ -108,7 +108,9 @@ typedef enum fmm_orient { FMM_CSR = 0, FMM_CSC = 1 } fmm_orient;
  * policy, any other with the default policy; NULL gathers every row with the default
  * policy.  Rows of hub lines, which many entries gather, then keep their place in L2
  * and the MALL instead of being displaced by rows that are gathered once.  It changes
- * only the cache policy of loads, so results are bit-identical with and without it.
+ * only the cache policy of loads, so results are bit-identical with and without it.  It
+ * is followed where a line has 64 lanes (fmm_launch_shape) and left aside with fewer, where
+ * it gained nothing.
  *
  * variant: how many stored entries a lane group keeps in flight per batch (FMM_VARIANT_*).
  * Deep batches suit long, uniform lines; shallow ones use fewer registers, so more lines

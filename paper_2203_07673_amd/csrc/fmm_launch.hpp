@@ -30,7 +30,14 @@ template <int OP, int NV, int CLS> constexpr int unroll_for() {
 constexpr int32_t kWaveChunks = 1 << 14;
 template <class Acc, int L> constexpr bool has_wave_kernel() { return L < 64 && sizeof(Acc) == 4; }
 
-template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, bool WAVE = false>
+// Whether gather hints are followed: where a wave holds a row.  R-MAT scale 22, 16 per row,
+// float32, in us without / with hints for 32 MB of rows: r = 256 (64 lanes) 9217 / 8973 forward,
+// 17817 / 17574 column pass; scale 20, r = 512 4468 / 4265 and 9255 / 8919.  With fewer lanes a
+// row the branch costs more than the kept rows give, in every pass: r = 128 5036 / 5144 and 9132 /
+// 9183, r = 64 3066 / 3282 and 5315 / 5714, bfloat16 r = 256 5918 / 5980 and 13883 / 14083.
+constexpr bool has_hints(int lanes) { return lanes == 64; }
+
+template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, bool WAVE = false, bool HINT = false>
 hipError_t launch_one(const LineArgs &a, hipStream_t stream)
 {
     constexpr int GPB = kBlock / L;
@@ -44,7 +51,7 @@ hipError_t launch_one(const LineArgs &a, hipStream_t stream)
         hipLaunchKernelGGL((line_wave_kernel<OP, TH, TG1, TG2, Acc, L, NV, VW, U>), dim3((unsigned)nb), dim3(kBlock), 0,
                            stream, a, (int32_t)nb_chunk);
     else
-        hipLaunchKernelGGL((line_kernel<OP, TH, TG1, TG2, Acc, L, NV, VW, U>), dim3((unsigned)nb), dim3(kBlock), 0,
+        hipLaunchKernelGGL((line_kernel<OP, TH, TG1, TG2, Acc, L, NV, VW, U, HINT>), dim3((unsigned)nb), dim3(kBlock), 0,
                            stream, a, (int32_t)nb_chunk);
     return hipGetLastError();
 }
@@ -54,6 +61,8 @@ hipError_t launch_kind(const LineArgs &a, hipStream_t stream)
 {
     if constexpr (has_wave_kernel<Acc, L>())
         if (a.n_chunks >= kWaveChunks) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, true>(a, stream);
+    if constexpr (has_hints(L))
+        if (a.hot) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, false, true>(a, stream);
     return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U>(a, stream);
 }
 

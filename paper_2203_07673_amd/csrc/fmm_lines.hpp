@@ -30,9 +30,9 @@
 // sum, so no broadcast is needed and no LDS is touched.  U entries are loaded
 // before any of them is reduced, to keep U row gathers in flight per group.
 //
-// Gather hints: with a per-entry hint array, entries whose hint is 0 gather their row
-// with the streaming (nontemporal) policy, so rows gathered once do not displace the
-// rows of hub lines, which many entries gather, from L2 and the MALL.
+// Gather hints (HINT): entries whose hint byte is 0 gather their row with the streaming
+// (nontemporal) policy, so rows gathered once do not displace the rows of hub lines, which
+// many entries gather, from L2 and the MALL.
 //
 // Long lines: with a split schedule, lines longer than long_len are skipped by
 // the line groups and processed as chunks (line, begin, end) whose partial
@@ -54,7 +54,6 @@ typedef uint16_t bf16_t;
 static __device__ const float kUnitF[1] = {1.0f};
 static __device__ const double kUnitD[1] = {1.0};
 static __device__ const int32_t kZeroIdx[1] = {0};
-static __device__ const uint8_t kHotByte[1] = {1};
 template <class Acc> __device__ __forceinline__ const Acc *unit_value();
 template <> __device__ __forceinline__ const float *unit_value<float>() { return kUnitF; }
 template <> __device__ __forceinline__ const double *unit_value<double>() { return kUnitD; }
@@ -292,16 +291,13 @@ template <int VW> __device__ __forceinline__ void st_bf16(bf16_t *p, const float
 // the first rep elements (RowVec below; the types that rows of any length use).
 template <class T, int VW> struct Raw;
 
-// The streaming load of a hinted gather stands in the other arm of a branch with the same load
-// without the hint; the compiler merges two such loads into one without it unless their
-// addresses differ to its eyes.  They do where a wave holds a row (L = 64), whose rows are wide
-// enough for hints to pay: R-MAT s22, r = 256, hinted column pass 17.47 ms apart, 18.05 merged.
-// Narrower groups gain more from the merged load without hints (R-MAT s17, r = 64, a step 223
-// us apart, 197 merged; s20, r = 64, bfloat16 1160, 1129).
-template <int L, class T> __device__ __forceinline__ const T *apart(const T *p)
+// A condition that the compiler cannot relate to x: the two loads of a hinted gather stand
+// behind x and behind its opposite, not in the arms of one branch, where the compiler joins
+// them into one load without the hint.
+__device__ __forceinline__ uint32_t opaque(uint32_t x)
 {
-    if constexpr (L == 64) asm("" : "+v"(p));
-    return p;
+    asm("" : "+v"(x));
+    return x;
 }
 template <> struct Raw<float, 1> {
     float x;
@@ -571,7 +567,7 @@ struct LineOperands {
     const void *H2;  // OP_FUSED1S, OP_FUSED1D: second held matrix
     void *out2;      // OP_FUSED1D: second output matrix
     bool out16;      // dst is bfloat16
-    const uint8_t *hot;  // per-entry gather hint (NULL: every row with the default policy)
+    const uint8_t *hot;  // per-entry gather hint (HINT)
     void *R;         // per-entry output (nnz): OP_SDDMM, OP_FUSED1S
     int32_t r;
     double beta;
@@ -581,7 +577,8 @@ struct LineOperands {
 // line (GPL > 1: wavefront-per-line; group gidx takes every GPL-th batch of U entries
 // and the partial sums are added across groups at the end).  dst receives the line's
 // r-vector (beta applied when keep_beta); OP_SDDMM writes per-entry values instead.
-template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, int GPL, bool PF = true>
+template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, int GPL, bool PF = true,
+          bool HINT = false>
 __device__ __forceinline__ void process_line(const LineOperands &o, int lane, int gidx, int32_t line, int32_t begin,
                                              int32_t end, Acc *dst, bool keep_beta)
 {
@@ -682,8 +679,6 @@ __device__ __forceinline__ void process_line(const LineOperands &o, int lane, in
     const int32_t w2s = wv2 ? 1 : 0;
     const int32_t *perm_p = wperm ? wperm : zero_index();
     const int32_t ps = wperm ? 1 : 0;
-    const uint8_t *hot_p = o.hot ? o.hot : kHotByte;
-    const int32_t hs = o.hot ? 1 : 0;
     const bool partial = r <= (L * NV - 1) * VW;  // some lanes own no vector of r (uniform)
 
     // Per-entry operands of one batch (column indices and weights).  Entries past `end`
@@ -695,7 +690,7 @@ __device__ __forceinline__ void process_line(const LineOperands &o, int lane, in
             const int32_t p = p0 + u;
             const int32_t pc = (FULL || p < end) ? p : end - 1;
             j[u] = ld_hint<kNtMeta>(idx + pc);
-            hv[u] = hot_p[pc * hs];
+            if constexpr (HINT) hv[u] = o.hot[pc];
             const Acc base = ld_hint<kNtMeta>(val_p + pc * vs);
             if constexpr (OP == OP_SPMM1 || OP == OP_SPMM2) {
                 const int32_t q = perm_p[pc * ps] + pc * (1 - ps);
@@ -733,12 +728,13 @@ __device__ __forceinline__ void process_line(const LineOperands &o, int lane, in
             for (int v = 0; v < NV; ++v) {
                 const int o = rv[v].off;  // idle lanes read a valid spot, zeroed below
                 if (FULL || okv[u]) {
-                    if (hv[u]) {
+                    if (!HINT || hv[u]) {
                         g1[u][v].load(row1 + o);
                         if constexpr (kTwo) g2[u][v].load(row2 + o);
-                    } else {
-                        g1[u][v].load_nt(apart<L>(row1 + o));
-                        if constexpr (kTwo) g2[u][v].load_nt(apart<L>(row2 + o));
+                    }
+                    if (HINT && !opaque(hv[u])) {
+                        g1[u][v].load_nt(row1 + o);
+                        if constexpr (kTwo) g2[u][v].load_nt(row2 + o);
                     }
                 }
             }
@@ -920,7 +916,7 @@ __device__ __forceinline__ void process_line(const LineOperands &o, int lane, in
                     j[u] = jn[u];
                     w1[u] = w1n[u];
                     w2[u] = w2n[u];
-                    hv[u] = hvn[u];
+                    if constexpr (HINT) hv[u] = hvn[u];
                 }
             }
         }
@@ -995,7 +991,7 @@ template <int OP> __device__ __forceinline__ LineOperands line_operands(const Li
     return o;
 }
 
-template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U>
+template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, bool HINT = false>
 __global__ __launch_bounds__(kBlock) void line_kernel(LineArgs a, int32_t nb_chunk_blocks)
 {
     constexpr int GPB = kBlock / L;  // groups per block
@@ -1025,8 +1021,8 @@ __global__ __launch_bounds__(kBlock) void line_kernel(LineArgs a, int32_t nb_chu
     }
     LineOperands o = line_operands<OP>(a);
     if (to_partial) o.out16 = false;
-    process_line<OP, TH, TG1, TG2, Acc, L, NV, VW, U, 1>(o, lane, 0, line, begin, end, dst,
-                                                         !to_partial && a.beta != 0.0);
+    process_line<OP, TH, TG1, TG2, Acc, L, NV, VW, U, 1, true, HINT>(o, lane, 0, line, begin, end, dst,
+                                                                     !to_partial && a.beta != 0.0);
 }
 
 // The line kernel of a pattern with many chunks of split lines, where a group is less than a

@@ -261,7 +261,8 @@ class Pattern:
         """Gather hints for one orientation (the library's fmm_gather_hints): entries whose
         minor line is among the `top` longest gather their row with the default cache
         policy, the others with the streaming policy, so the rows many entries gather stay
-        in L2 and the MALL.  top None or 0 removes the hints.  Results are unchanged."""
+        in L2 and the MALL.  top None or 0 removes the hints.  Results are unchanged.  Calls
+        with fewer than 64 lanes a line (launch_shape) leave the hints aside."""
         if not top:
             self._hints[orient] = None
         else:
@@ -418,8 +419,9 @@ class Pattern:
 
         longest = max(self.max_line(C.FMM_CSR), self.max_line(C.FMM_CSC))
         cands = [ll for ll in split_candidates if ll < longest] if self._split else []
-        # gather hints are tried where the gathered rows have hubs
-        skewed = {o: self.minor_skewed(o) for o in (C.FMM_CSR, C.FMM_CSC)}
+        # gather hints are tried where the gathered rows have hubs and the passes follow hints
+        skewed = {o: self.launch_shape(o, False, r, dcode)[0] == 64 and self.minor_skewed(o)
+                  for o in (C.FMM_CSR, C.FMM_CSC)}
         top = max(1, HINT_BYTES // (r * A.element_size()))
         hints = (None, top) if hint_candidates and any(skewed.values()) else (None,)
         combos = [(lo, ll, h) for lo in orders for ll in (cands or [None]) for h in hints]
