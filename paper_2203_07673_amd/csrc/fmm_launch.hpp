@@ -100,33 +100,16 @@ template <class TH, class TG1, class TG2> constexpr int vector_width() {
     return 16 / mn;
 }
 
-// Whether a fused pass leaves the line order aside.  The order lets lines of like length share
-// a wave; it costs the held rows and outputs, which then come from all over their arrays.
-// With a wave per line there is nothing to share, and above 2^18 lines the pass is faster in
-// index order: R-MAT, 16 per row, r = 256, float32, ordered / not, forward and column pass:
-// 2^16 lines 101 / 112 and 208 / 222 us (longest lines first still pays), 2^18 490 / 471 and
-// 1031 / 1021, 2^20 2463 / 2161 and 4911 / 4613, 2^22 10465 / 9820 and 19107 / 18455.  With two
-// lines a wave the two-row pass, which reads a wider row per entry, gains above 2^20 lines: r =
-// 128 2182 / 2100, bfloat16 r = 256 3599 / 3331; the one-row pass does not (1094 / 1085, 1262 /
-// 1315).  SDDMM and SpMM are within 2% either way at 64 lanes and lose at 32.
-template <int OP> constexpr bool index_order(int lanes, int64_t nlines)
-{
-    if (OP != OP_FUSED1 && OP != OP_FUSED2 && OP != OP_FUSED1S) return false;
-    return (lanes == 64 && nlines >= (1 << 18)) || (lanes == 32 && OP == OP_FUSED2 && nlines >= (1 << 20));
-}
-
 template <int OP, class TH, class TG1, class TG2, class Acc>
-hipError_t launch_lines(const LineArgs &args, int32_t n_splits, const int32_t *splits, Shape hint,
+hipError_t launch_lines(const LineArgs &a, int32_t n_splits, const int32_t *splits, Shape hint,
                         hipStream_t stream)
 {
-    LineArgs a = args;
     constexpr int VWV = vector_width<TH, TG1, TG2>();
     constexpr bool has_bf16 = sizeof(TH) == 2 || sizeof(TG1) == 2 || sizeof(TG2) == 2;
     const bool vector_path = vector_rows(a.r, VWV);
     const int vw = vector_path ? VWV : 1;
     const Shape shape = vw > 1 && shape_supported(hint, a.r, vw) ? hint : default_shape(a.r, vw);
     if (!shape_supported(shape, a.r, vw)) return hipErrorInvalidValue;
-    if (index_order<OP>(shape.L, a.nlines)) a.order = nullptr;
     hipError_t e;
     if (vector_path) {
         e = launch_shape<OP, TH, TG1, TG2, Acc, VWV>(a, shape, stream);

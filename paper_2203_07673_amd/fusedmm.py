@@ -108,7 +108,8 @@ class Pattern:
     orientations, and each orientation's line processing order by decreasing length
     (fmm_line_order).  ``line_order`` is True, False or None (the default: on for an
     orientation whose longest line exceeds four times its mean length, where lines of
-    very different lengths would share wavefronts).  ``autotune`` picks the split
+    very different lengths would share wavefronts; fused passes over wide rows leave that
+    default aside, see _fused_desc).  ``autotune`` picks the split
     threshold, the order and the batch depth per orientation by timing.  The pattern is
     validated once at construction; later calls trust it.
     """
@@ -137,6 +138,7 @@ class Pattern:
         self._csc_sched = None
         self._split = split
         self._orders = {C.FMM_CSR: None, C.FMM_CSC: None}
+        self._order_chosen = {o: line_order is not None for o in self._orders}
         self._hints = {C.FMM_CSR: None, C.FMM_CSC: None}  # (top, per-entry uint8 tensor)
         self._hint_cache = {}
         self._ws_cache = {}
@@ -246,6 +248,7 @@ class Pattern:
             raise TypeError(f"values must be {self.val_dtype} on {self.device}")
         Q = copy.copy(self)
         Q._orders = dict(self._orders)  # Q's own tuning changes must not swap tensors under self's descriptors
+        Q._order_chosen = dict(self._order_chosen)
         Q._hints = dict(self._hints)
         Q.val = s.detach().contiguous()
         Q.valT = torch.empty(max(1, self.nnz), dtype=self.val_dtype, device=self.device)
@@ -294,6 +297,7 @@ class Pattern:
     def set_line_order(self, orient, enabled: bool):
         """Process one orientation's lines by decreasing length (True) or in index order."""
         self._orders[orient] = self._order(orient, self._long_len(orient)) if enabled else None
+        self._order_chosen[orient] = True
         self._wait()
         self._refresh(orient)
 
@@ -320,6 +324,27 @@ class Pattern:
             d.order = self._orders[orient].data_ptr()
         if self._hints.get(orient) is not None:
             d.hot = self._hints[orient][1].data_ptr()
+        return d
+
+    def _fused_desc(self, orient, two_row, X):
+        """Descriptor for a fused pass with storage like X.  A line order that nobody chose is
+        left out where rows are wide and lines many: with a wave per line there is no wave to
+        share, and the order scatters the held rows and outputs over their arrays.  R-MAT and
+        Zipf row lengths, 4 to 48 per row, float32 at r = 256, ordered / index order in us: 2^18
+        lines 490 / 471 and (two-row pass) 1031 / 1021, 2^20 2397 / 2194 and 4679 / 4352, 2^22 10465
+        / 9820 and 19107 / 18455; bfloat16 r = 512, 2^20 2648 / 2563 and 7290 / 6786.  Rows that
+        leave lanes idle are better ordered, r = 160: 2^18 lines, 4 per row 126 / 168 and 179 / 229,
+        2^20 1443 / 1487 and 2696 / 2645.  With two lines a wave (512-byte rows) the two-row pass
+        gains above 2^20 lines, r = 128 915 / 871, bfloat16 r = 256 3535 / 3267; the one-row pass
+        does not (2340 / 2430)."""
+        d = self.csr if orient == C.FMM_CSR else self.csc
+        if not d.order or self._order_chosen[orient] or X.dtype == torch.float64:
+            return d
+        lines = self.m if orient == C.FMM_CSR else self.n
+        row = X.shape[1] * X.element_size()
+        if (row >= 1024 and lines >= 1 << 18) or (two_row and row == 512 and lines >= 1 << 20):
+            d = C.fmm_sparse.from_buffer_copy(d)
+            d.order = None
         return d
 
     def descriptor(self, orient, schedule=True):
@@ -547,7 +572,8 @@ def fusedmm_a_raw(P, A, B, out=None, fused=True, R_ws=None):
     elif R_ws is not None:
         _check_buf("R_ws", R_ws, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A, r, dcode)
-    C.call("fmm_fusedmm_a", ctypes.byref(P.csr), _ptr(A), _ptr(B), r, dcode, _ptr(out),
+    csr = P._fused_desc(C.FMM_CSR, False, A) if fused else P.csr
+    C.call("fmm_fusedmm_a", ctypes.byref(csr), _ptr(A), _ptr(B), r, dcode, _ptr(out),
            C.FMM_FUSED if fused else C.FMM_UNFUSED, _ptr(R_ws), _ptr(ws), wb, _stream())
     return out, R_ws
 
@@ -562,7 +588,8 @@ def fusedmm_a_noalloc_raw(P, A, B, out):
     _check_dense("B", B, P.n, r, P.device)
     dcode, odt = _common(P, A, B)
     _check_buf("out", out, P.device, odt, (P.m, r))
-    C.call("fmm_fusedmm_a_noalloc", ctypes.byref(P.csr), _ptr(A), _ptr(B), r, dcode, _ptr(out), _stream())
+    csr = P._fused_desc(C.FMM_CSR, False, A)
+    C.call("fmm_fusedmm_a_noalloc", ctypes.byref(csr), _ptr(A), _ptr(B), r, dcode, _ptr(out), _stream())
     return out
 
 
@@ -583,7 +610,8 @@ def fusedmm_b_raw(P, A, B, out=None, fused=True, R_ws=None):
     elif R_ws is not None:
         _check_buf("R_ws", R_ws, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_B, r, dcode)
-    C.call("fmm_fusedmm_b", ctypes.byref(P.csc), _ptr(A), _ptr(B), r, dcode, _ptr(out),
+    csc = P._fused_desc(C.FMM_CSC, False, A) if fused else P.csc
+    C.call("fmm_fusedmm_b", ctypes.byref(csc), _ptr(A), _ptr(B), r, dcode, _ptr(out),
            C.FMM_FUSED if fused else C.FMM_UNFUSED, _ptr(R_ws), _ptr(ws), wb, _stream())
     return out, R_ws
 
@@ -627,8 +655,11 @@ def _fused_backward(form, P, A, B, dC, dA, dB, need, fused, R_ws, dP_ws, grad16=
         if buf is not None:
             _check_buf(name, buf, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A_BWD if form == "a" else C.FMM_OP_FUSEDMM_B_BWD, r, dcode)
-    C.call("fmm_fusedmm_a_backward" if form == "a" else "fmm_fusedmm_b_backward", ctypes.byref(P.csr),
-           ctypes.byref(P.csc), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dA if need[0] else None),
+    csr, csc = P.csr, P.csc
+    if fused:  # the one-row pass runs on the form's own orientation, the two-row pass on the other
+        csr, csc = P._fused_desc(C.FMM_CSR, form == "b", A), P._fused_desc(C.FMM_CSC, form == "a", A)
+    C.call("fmm_fusedmm_a_backward" if form == "a" else "fmm_fusedmm_b_backward", ctypes.byref(csr),
+           ctypes.byref(csc), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dA if need[0] else None),
            _ptr(dB if need[1] else None), flags, _ptr(R_ws), _ptr(dP_ws), _ptr(ws), wb, _stream())
     return dA, dB
 
@@ -673,12 +704,14 @@ def _values_backward(form, P, A, B, dC, dS, dX, want_dX, fused, grad16=False):
     flags = (C.FMM_FUSED if fused else C.FMM_UNFUSED) | (C.FMM_GRAD_BF16 if grad16 else 0)
     out = _ptr(dX if want_dX else None)
     if form == "a":
+        csr = P._fused_desc(C.FMM_CSR, False, A) if fused else P.csr
         ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A_BWD_VALUES, r, dcode)
-        C.call("fmm_fusedmm_a_backward_values", ctypes.byref(P.csr), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dS),
+        C.call("fmm_fusedmm_a_backward_values", ctypes.byref(csr), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dS),
                out, flags, _ptr(ws), wb, _stream())
     else:
+        csc = P._fused_desc(C.FMM_CSC, False, A) if fused else P.csc
         ws, wb = P.workspace(C.FMM_OP_FUSEDMM_B_BWD_VALUES, r, dcode)
-        C.call("fmm_fusedmm_b_backward_values", ctypes.byref(P.csr), ctypes.byref(P.csc), _ptr(A), _ptr(B), _ptr(dC), r,
+        C.call("fmm_fusedmm_b_backward_values", ctypes.byref(P.csr), ctypes.byref(csc), _ptr(A), _ptr(B), _ptr(dC), r,
                dcode, _ptr(dS), out, flags, _ptr(ws), wb, _stream())
     return dS[:P.nnz], (dX if want_dX else None)
 
