@@ -142,6 +142,8 @@ LineArgs base_args(const fmm_sparse *S, int32_t r, void *ws)
     memset(&a, 0, sizeof(a));
     a.uclass = unroll_class(S);
     a.nlines = nmajor(S);
+    a.nminor = nminor(S);
+    a.nnz = S->nnz;
     a.r = r;
     a.ptr = S->ptr;
     a.idx = S->idx;
@@ -947,15 +949,14 @@ fmm_status fmm_launch_shape(const fmm_sparse *S, int32_t two_row, int32_t r, int
     if (!lanes || !nv || !vw || !unroll) return FMM_ERR_NULL;
     // the vector width follows the narrowest operand: bfloat16 storage gives 8, else 16 / element
     const int vwv = k.path == PATH_BF16 ? 8 : k.path == PATH_F64 ? 2 : 4;
-    const int w = vector_rows(r, vwv) ? vwv : 1;
-    const Shape hs{tuning().lanes, tuning().nv};
-    const Shape sh = w > 1 && shape_supported(hs, r, w) ? hs : default_shape(r, w);
+    const LineShape ls = line_shape(base_args(S, r, nullptr), two_row ? 2 : 1, vwv, hint());
+    const Shape sh = ls.shape;
     const int cls = unroll_class(S);
     const int one = cls == 1 ? 8 : cls == 2 ? 4 : 2;
     int u = (two_row ? one / 2 : one) / sh.NV;
     *lanes = sh.L;
     *nv = sh.NV;
-    *vw = w;
+    *vw = ls.vw;
     *unroll = u < 1 ? 1 : u;
     return FMM_OK;
 }

@@ -18,14 +18,42 @@ struct Shape {
 };
 
 // Rows in 16-byte vectors of vw elements, or one element per lane.  A row whose length is no
-// multiple of the vector ends in one that overlaps the one before (RowVec).  That pays above
-// 16 elements (64 bytes): on 2^17 x 2^17 R-MAT, 16 per row, float32, the forward and the column
-// pass take 63 and 113 us at r = 50 (113 and 164 with an element per lane, a wave for a line),
-// 49 and 75 us at r = 17 (62 and 83).  Below, element by element keeps more lanes on a line,
-// which read its indices together: r = 9, 42 and 64 us against 50 and 71.  Where the rows come
-// from beyond L2 the two are within a few percent (300k x 200k, 30 per row, r = 50: 371 and 801
-// us against 388 and 757).
+// multiple of the vector ends in one that overlaps the one before (RowVec).  That can pay above
+// 16 elements (64 bytes).  Below, element by element keeps more lanes on a line, which read its
+// indices together: 2^17 x 2^17 R-MAT, 16 per row, r = 9, forward and column pass 42 and 64 us
+// by elements against 50 and 71 in vectors.
 inline bool vector_rows(int r, int vw) { return r % vw == 0 || r * (16 / vw) > 64; }
+
+// What a line pass takes of the two, by the rows it gathers per entry: 2 (OP_FUSED2, OP_SPMM2),
+// 1 (OP_FUSED1, and OP_SPMM1 with weights read through a permutation) or 0 (the others, always
+// in vectors).  Vectors that start at any element take more cache accesses for a row than
+// dwords do; they win where the row leaves many of the 32 or 64 lanes of the other form idle,
+// where lines are short (more of them share a wave), and where the gathered rows mostly hit L2,
+// as on power-law patterns (which have split lines).  float32, elements / vectors in us:
+//   fused forward  uniform, 300k, 30 per row: r = 21 237 / 246, 27 273 / 284, 33 376 / 301;
+//                  2^17, 16 per row: r = 21 (11 MB) 59 / 53, 27 (14 MB) 62 / 66; 2^18, 8 per
+//                  row: r = 27 81 / 71; R-MAT 2^19, 16 per row: r = 25 235 / 184
+//   weights by permutation  uniform, 300k, 30 per row: r = 17 368 / 386, 27 420 / 448, 33 468 /
+//                  464; 2^17, 16 per row: r = 17 (9 MB) 81 / 86; with weights in order, 300k:
+//                  r = 17 253 / 221, 27 280 / 283, 33 424 / 302
+//   two rows       uniform, 300k, 30 per row: r = 17 433 / 475, 27 545 / 599, 38 641 / 671, 61
+//                  894 / 929, 75 1018 / 1039; 60k, 30 per row: r = 21 (10 MB) 74 / 78, 38 (18 MB)
+//                  125 / 115; 2^17, 16 per row: r = 38 (40 MB) 158 / 150, 61 (64 MB) 205 / 212;
+//                  2^18, 8 per row: r = 46 190 / 184; 2^20, 16 per row: r = 50 (420 MB) 1514 /
+//                  1489; R-MAT 2^17, 16 per row: r = 17 80 / 73, 46 165 / 107
+//   no rule needed  dS with its gradient, 300k: r = 17 398 / 250, 31 410 / 326; SDDMM 268 / 240
+//                  and 313 / 320
+// Wider rows of a two-row pass lie within 2% either way.  float64 stays in vectors.
+inline bool line_vectors(const LineArgs &a, int rows, int vw)
+{
+    const int r = a.r;
+    if (r % vw == 0 || vw != 4 || r <= 16) return vector_rows(r, vw);
+    if (rows == 0 || a.n_chunks > 0 || r > 32 * rows) return true;
+    const double mb = 1e-6 * rows * 4 * r * a.nminor;  // of gathered matrices
+    const bool short_lines = (double)a.nnz < 12.0 * a.nlines;
+    if (rows == 1) return short_lines || mb <= (a.wperm ? 8 : 12);
+    return r <= 32 ? mb <= 8 : short_lines || mb <= 48 || mb > 400;
+}
 
 // Chosen by the launcher from r (and the vector width vw) unless a valid hint is given.
 // A shape is supported when it is one of the compiled ones and L * NV vectors of vw
@@ -33,6 +61,21 @@ inline bool vector_rows(int r, int vw) { return r % vw == 0 || r * (16 / vw) > 6
 Shape default_shape(int r, int vw);
 bool shape_supported(Shape s, int r, int vw);
 int max_r(int path, int r);  // 0 when r is not supported for the dtype path
+
+// The form of a pass: elements per vector and lane-group shape.  A shape given by hint that
+// covers r in vectors is taken as it is.
+struct LineShape {
+    int vw;
+    Shape shape;
+};
+inline LineShape line_shape(const LineArgs &a, int rows, int vw, Shape hint)
+{
+    if (vector_rows(a.r, vw)) {
+        if (shape_supported(hint, a.r, vw)) return {vw, hint};
+        if (line_vectors(a, rows, vw)) return {vw, default_shape(a.r, vw)};
+    }
+    return {1, default_shape(a.r, 1)};
+}
 
 // Tuning knobs (process-wide; set through fmm_set_tuning for experiments and the autotuner).
 struct Tuning {

@@ -8,12 +8,14 @@
 
 namespace fmm {
 
+template <int OP> constexpr bool two_row() { return OP == OP_SPMM2 || OP == OP_FUSED2; }
+
 // Entries loaded ahead per group: enough gathers in flight without spilling.  A lane
 // holds U * NV vectors of 16 bytes per gathered matrix.
 // Batch depth of class CLS (1 deep, 2 medium, 3 shallow): entries per batch for the
 // one-row passes, half that for the two-row passes, divided by the vectors per lane.
 template <int OP, int NV, int CLS> constexpr int unroll_for() {
-    constexpr bool two = (OP == OP_SPMM2 || OP == OP_FUSED2);
+    constexpr bool two = two_row<OP>();
     constexpr int one = CLS == 1 ? 8 : CLS == 2 ? 4 : 2;
     constexpr int u = (two ? one / 2 : one) / NV;
     return u < 1 ? 1 : u;
@@ -59,7 +61,7 @@ hipError_t launch_one(const LineArgs &a, hipStream_t stream)
 template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U>
 hipError_t launch_kind(const LineArgs &a, hipStream_t stream)
 {
-    if constexpr (has_wave_kernel<Acc, L>())
+    if constexpr (has_wave_kernel<Acc, L>() && !(VW == 1 && L == 32))  // without split lines (line_vectors)
         if (a.n_chunks >= kWaveChunks) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, true>(a, stream);
     if constexpr (has_hints(L))
         if (a.hot) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, false, true>(a, stream);
@@ -81,9 +83,11 @@ hipError_t launch_shape(const LineArgs &a, Shape shape, hipStream_t stream)
     FMM_SHAPE_CASE(4, 1)
     FMM_SHAPE_CASE(8, 1)
     FMM_SHAPE_CASE(16, 1)
-    if constexpr (VW > 1) {  // one element per lane: up to 16 of them (vector_rows)
-        FMM_SHAPE_CASE(32, 1)
-        FMM_SHAPE_CASE(64, 1)
+    // one element per lane: up to 16 of them, in float32 up to 32 or 64 (line_vectors)
+    constexpr bool two = sizeof(Acc) == 4 && two_row<OP>(), one = sizeof(Acc) == 4 && (OP == OP_FUSED1 || OP == OP_SPMM1);
+    if constexpr (VW > 1 || one || two) { FMM_SHAPE_CASE(32, 1) }
+    if constexpr (VW > 1 || two) { FMM_SHAPE_CASE(64, 1) }
+    if constexpr (VW > 1) {
         FMM_SHAPE_CASE(16, 2)
         FMM_SHAPE_CASE(32, 2)
         FMM_SHAPE_CASE(64, 2)
@@ -106,12 +110,11 @@ hipError_t launch_lines(const LineArgs &a, int32_t n_splits, const int32_t *spli
 {
     constexpr int VWV = vector_width<TH, TG1, TG2>();
     constexpr bool has_bf16 = sizeof(TH) == 2 || sizeof(TG1) == 2 || sizeof(TG2) == 2;
-    const bool vector_path = vector_rows(a.r, VWV);
-    const int vw = vector_path ? VWV : 1;
-    const Shape shape = vw > 1 && shape_supported(hint, a.r, vw) ? hint : default_shape(a.r, vw);
+    const int rows = two_row<OP>() ? 2 : OP == OP_FUSED1 || (OP == OP_SPMM1 && a.wperm) ? 1 : 0;
+    const auto [vw, shape] = line_shape(a, rows, VWV, hint);
     if (!shape_supported(shape, a.r, vw)) return hipErrorInvalidValue;
     hipError_t e;
-    if (vector_path) {
+    if (vw > 1) {
         e = launch_shape<OP, TH, TG1, TG2, Acc, VWV>(a, shape, stream);
     } else {
         if constexpr (has_bf16) {

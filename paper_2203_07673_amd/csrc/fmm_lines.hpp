@@ -65,6 +65,7 @@ constexpr int kBlock = 256;
 
 struct LineArgs {
     int32_t nlines;
+    int32_t nminor, nnz;  // for the launcher's choices
     int32_t r;
     const int32_t *ptr;
     const int32_t *idx;
