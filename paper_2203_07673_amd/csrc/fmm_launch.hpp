@@ -128,11 +128,11 @@ hipError_t launch_lines(const LineArgs &a, int32_t n_splits, const int32_t *spli
         const Acc *partial = static_cast<const Acc *>(a.partial);
         if constexpr (has_bf16) {
             if (a.out16)
-                return launch_merge<Acc>(splits, n_splits, a.r, partial, MergeBf16{static_cast<bf16_t *>(a.out), a.r},
-                                         stream);
+                return launch_merge<Acc>(splits, n_splits, a.n_chunks, a.r, partial,
+                                         MergeBf16{static_cast<bf16_t *>(a.out), a.r}, stream);
         }
-        e = launch_merge<Acc>(splits, n_splits, a.r, partial, MergePlain<Acc>{static_cast<Acc *>(a.out), a.beta, a.r},
-                              stream);
+        e = launch_merge<Acc>(splits, n_splits, a.n_chunks, a.r, partial,
+                              MergePlain<Acc>{static_cast<Acc *>(a.out), a.beta, a.r}, stream);
     }
     return e;
 }

@@ -301,6 +301,16 @@ template <class Acc> struct MergeSoftmax {
         if (writes && lse && lane == 0) lse[line] = L > Acc(0) ? M + log_acc<Acc>(L) : Acc(0);
         return State{M, L > Acc(0) ? Acc(1) / L : Acc(0)};
     }
+    __device__ __forceinline__ State begin_few(int32_t line, int32_t first, int32_t cnt, bool writes) const {
+        Acc M = neg_inf<Acc>(), L = Acc(0);
+        for (int32_t c = first; c < first + cnt; ++c) {
+            const Acc m = ml[2 * (size_t)c];
+            M = m > M ? m : M;
+        }
+        for (int32_t c = first; c < first + cnt; ++c) L += ml[2 * (size_t)c + 1] * exp_acc<Acc>(ml[2 * (size_t)c] - M);
+        if (writes && lse) lse[line] = L > Acc(0) ? M + log_acc<Acc>(L) : Acc(0);
+        return State{M, L > Acc(0) ? Acc(1) / L : Acc(0)};
+    }
     __device__ __forceinline__ Acc weigh(const State &st, int32_t chunk, Acc x) const {
         return x * exp_acc<Acc>(ml[2 * (size_t)chunk] - st.M);
     }
@@ -316,10 +326,11 @@ hipError_t merge_rows(const fmm_sparse *S, int32_t r, bool softmax, const void *
 {
     const Acc *partial = static_cast<const Acc *>(ws);
     if (softmax)
-        return launch_merge<Acc>(S->splits, S->n_splits, r, partial,
+        return launch_merge<Acc>(S->splits, S->n_splits, S->n_chunks, r, partial,
                                  MergeSoftmax<Acc>{static_cast<Acc *>(out), static_cast<Acc *>(lse),
                                                    partial + (size_t)S->n_chunks * r, r}, st);
-    return launch_merge<Acc>(S->splits, S->n_splits, r, partial, MergePlain<Acc>{static_cast<Acc *>(out), 0.0, r}, st);
+    return launch_merge<Acc>(S->splits, S->n_splits, S->n_chunks, r, partial,
+                             MergePlain<Acc>{static_cast<Acc *>(out), 0.0, r}, st);
 }
 
 template <class TH, class Acc, int L, int NV, int VW, int U, bool RAG>

@@ -470,6 +470,12 @@ template <class Acc> struct MergeColumns {
         if (writes && lane == 0) dt[line] = x;
         return State{ds ? ds[line] : Acc(0), x};
     }
+    __device__ __forceinline__ State begin_few(int32_t line, int32_t first, int32_t cnt, bool writes) const {
+        Acc x = Acc(0);
+        for (int32_t c = first; c < first + cnt; ++c) x += part_sc[c];
+        if (writes) dt[line] = x;
+        return State{ds ? ds[line] : Acc(0), x};
+    }
     __device__ __forceinline__ Acc weigh(const State &, int32_t, Acc x) const { return x; }
     template <int VW> __device__ __forceinline__ void store(const State &st, int32_t line, int k, Acc *v) const {
         if (ds) {
@@ -796,7 +802,7 @@ hipError_t run_bwd_shape(const fmm_sparse *S_csr, const fmm_sparse *S_csc, const
                            dim3(kBlock), 0, st, a, (int32_t)nbc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (split_rows) {
-            e = launch_merge<Acc>(S_csr->splits, S_csr->n_splits, 1, static_cast<const Acc *>(a.part_sc),
+            e = launch_merge<Acc>(S_csr->splits, S_csr->n_splits, S_csr->n_chunks, 1, static_cast<const Acc *>(a.part_sc),
                                   MergePlain<Acc>{ds, 0.0, 1}, st);
             if (e != hipSuccess) return e;
         }
@@ -834,7 +840,7 @@ hipError_t run_bwd_shape(const fmm_sparse *S_csr, const fmm_sparse *S_csc, const
                            (int32_t)nbc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (S_csc->n_chunks > 0 && S_csc->n_splits > 0) {
-        e = launch_merge<Acc>(S_csc->splits, S_csc->n_splits, r, static_cast<const Acc *>(a.part_vec),
+        e = launch_merge<Acc>(S_csc->splits, S_csc->n_splits, S_csc->n_chunks, r, static_cast<const Acc *>(a.part_vec),
                               MergeColumns<Acc>{static_cast<Acc *>(sums), dt, static_cast<const Acc *>(a.part_sc),
                                                 once ? nullptr : ds, a1, a2, r, out16 && !once},
                               st);
