@@ -29,8 +29,21 @@ template <int OP, int NV, int CLS> constexpr int unroll_for() {
 // 121, 7900 144 / 139, 10800 210 / 197, 11600 244 / 247, 16000 (r = 16) 201 / 212, 19800 414 /
 // 394 and (bfloat16) 317 / 305, 24300 (r = 32) 186 / 181, 29500 311 / 302, 129000 (r = 32, 64
 // per row) 825 / 745.
+//
+// A one-row pass by narrow groups needs chunks of full length besides: the groups of a wave
+// load 64 / L batches of U entries at once, more than a short chunk holds.  2^17 lines of 150,
+// chunks of 128 and 22, forward, group / wave: bfloat16 r = 16 257 / 333, r = 32 295 / 333, r = 64
+// (with float32 dC) 379 / 423, r = 128 695 / 678, float32 r = 8 254 / 279; lines of 250, chunks of
+// 128 and 122: bfloat16 r = 16 495 / 379, float32 r = 8 496 / 365.  Two-row passes gain either
+// way (bfloat16 r = 16, 150: 615 / 560).
 constexpr int32_t kWaveChunks = 1 << 14;
 template <class Acc, int L> constexpr bool has_wave_kernel() { return L < 64 && sizeof(Acc) == 4; }
+template <int OP, int L, int U> bool chunks_by_waves(const LineArgs &a)
+{
+    if (a.n_chunks < kWaveChunks) return false;
+    if (two_row<OP>() || 64 / L * U <= 32) return true;
+    return (double)a.nnz >= 0.75 * a.long_len * a.n_chunks;  // the entries bound the chunks' mean length
+}
 
 // Whether gather hints are followed: where a wave holds a row.  R-MAT scale 22, 16 per row,
 // float32, in us without / with hints for 32 MB of rows: r = 256 (64 lanes) 9217 / 8973 forward,
@@ -62,7 +75,7 @@ template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int 
 hipError_t launch_kind(const LineArgs &a, hipStream_t stream)
 {
     if constexpr (has_wave_kernel<Acc, L>() && !(VW == 1 && L == 32))  // without split lines (line_vectors)
-        if (a.n_chunks >= kWaveChunks) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, true>(a, stream);
+        if (chunks_by_waves<OP, L, U>(a)) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, true>(a, stream);
     if constexpr (has_hints(L))
         if (a.hot) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, false, true>(a, stream);
     return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U>(a, stream);
