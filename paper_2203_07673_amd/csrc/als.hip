@@ -87,9 +87,13 @@ struct CgArgs {
 // 64, 10 iterations: 3e-2 of B).  All sums keep one order for every kernel here: dot products
 // an FMA chain over a lane's elements and a tree over the lanes of the power of two of vectors
 // in a row, or for r of up to 64 that is no multiple of four a tree over elements; sums of
-// rows a chain in entry order, chunk by chunk for split lines.
+// rows a chain in entry order, chunk by chunk for split lines.  In float32 that is the order
+// of a pass of the line kernels per iteration.  Rows of over 64 elements in no whole vectors
+// have lanes of elements 64 apart for it, which costs (2^15 lines of 20, r = 99, 10 iterations:
+// 914 us, 471 in overlapping vectors; 1433 with a pass per iteration).  Chains of bfloat16 rows
+// are eight elements long.
 template <class TF, int L, int NV, int VW, bool RAG> struct LaneRow {
-    static constexpr bool kPairs = RAG && L <= 16;  // r of up to 64
+    static_assert(!RAG || L <= 16, "r of up to 64");
     bool act[NV], full;
     int off[NV], rep[NV];
     __device__ __forceinline__ LaneRow(int lane, int r) {
@@ -129,7 +133,7 @@ template <class TF, int L, int NV, int VW, bool RAG> struct LaneRow {
     }
     // this lane's part of <y, z>, for a y that went through once()
     template <class Get> __device__ __forceinline__ float part(const float *y, Get z) const {
-        if constexpr (kPairs) {
+        if constexpr (RAG) {
             float m[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) m[e] = fmadd(y[e], z(0, e), 0.f);
@@ -143,15 +147,50 @@ template <class TF, int L, int NV, int VW, bool RAG> struct LaneRow {
             for (int e = 0; e < VW; ++e) s = fmadd(y[v * VW + e], z(v, e), s);
         return s;
     }
+    __device__ __forceinline__ float dot(const float *y, const float *z) const {
+        float ym[NV * VW];
+        once(y, ym);
+        return group_sum<L>(part(ym, [&](int v, int e) { return z[v * VW + e]; }));
+    }
     // <y, y>, where the chain begins at the second element
-    __device__ __forceinline__ float squares(const float *y) const {
-        if constexpr (VW == 1 || kPairs) return part(y, [&](int v, int e) { return y[v * VW + e]; });
-        float s = fmadd(y[0], y[0], y[1 % (NV * VW)] * y[1 % (NV * VW)]);
+    __device__ __forceinline__ float square(const float *y) const {
+        float ym[NV * VW];
+        once(y, ym);
+        if constexpr (VW == 1 || RAG) return group_sum<L>(part(ym, [&](int v, int e) { return ym[v * VW + e]; }));
+        float s = fmadd(ym[0], ym[0], ym[1 % (NV * VW)] * ym[1 % (NV * VW)]);
 #pragma unroll
-        for (int e = 2; e < NV * VW; ++e) s = fmadd(y[e], y[e], s);
-        return s;
+        for (int e = 2; e < NV * VW; ++e) s = fmadd(ym[e], ym[e], s);
+        return group_sum<L>(s);
+    }
+    __device__ __forceinline__ void store(float *row, const float *y) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (act[v]) st_row<VW>(row + off[v], y + v * VW);
     }
 };
+
+// One CG step on a line's iterate x, residual res and direction p, with q = (sum_j F_j F_j^T) p and
+// rr = <res, res>; returns the new rr.
+template <class TF, int L, int NV, int VW, bool RAG>
+__device__ __forceinline__ float cg_step(const LaneRow<TF, L, NV, VW, RAG> &at, float lam, float rr, float *p, float *q,
+                                         float *x, float *res)
+{
+    constexpr int E = NV * VW;
+#pragma unroll
+    for (int e = 0; e < E; ++e) q[e] = fmadd(lam, p[e], q[e]);
+    const float pq = at.dot(p, q);
+    const float alpha = (rr > 0.f && pq > 0.f) ? rr / pq : 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        x[e] = fmadd(alpha, p[e], x[e]);
+        res[e] = fmadd(-alpha, q[e], res[e]);
+    }
+    const float rrn = at.square(res);
+    const float beta = rr > 0.f ? rrn / rr : 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) p[e] = fmadd(beta, p[e], res[e]);
+    return rrn;
+}
 
 // out += sum of c_u F_u over N rows, in order: c_u = <y, F_u> (DOT; y went through once()) or
 // w_u.  Entries from n on are left out.
@@ -186,6 +225,17 @@ __device__ __forceinline__ void add_rows(const LaneRow<TF, L, NV, VW, RAG> &at, 
     }
 }
 
+// The split lines' solve: iterate, residual and direction of every line, <residual, residual>, and
+// the chunks' partials.
+struct SplitCg {
+    const int32_t *splits;
+    int32_t n_splits, r;
+    float lambda;
+    const float *rhs;
+    float *X, *R, *P, *rr;
+    const float *partial;
+};
+
 // The whole CG solve of a line by a group of L lanes that holds an r-row, with the gathered
 // rows F_j in registers for every iteration.  A line's iterations depend on no other line, so
 // each row comes from memory once where a pass per iteration gathers it iters + 1 times (and
@@ -209,7 +259,7 @@ template <class TF, int L, int NV, int VW, bool RAG, int S, int SB>
 __global__ __launch_bounds__(kBlock, 2) void cg_resident_kernel(CgArgs a)
 {
     constexpr int E = NV * VW;
-    constexpr int OV = NV > 1 ? 2 : VW == 8 ? 4 : 8;  // rows in flight past the slots
+    constexpr int OV = VW == 1 ? 8 : NV > 1 ? 2 : VW == 8 ? 4 : 8;  // rows in flight past the slots
     static_assert(S % SB == 0, "whole blocks of slots");
     const int lane = threadIdx.x % L;
     const int64_t k = (int64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
@@ -282,17 +332,6 @@ __global__ __launch_bounds__(kBlock, 2) void cg_resident_kernel(CgArgs a)
             add_rows<DOT, OV>(at, o, len - t, ym, w, out);
         }
     };
-    auto dot = [&](const float *y, const float *z) {
-        float ym[E];
-        at.once(y, ym);
-        return group_sum<L>(at.part(ym, [&](int v, int e) { return z[v * VW + e]; }));
-    };
-    auto square = [&](const float *y) {
-        float ym[E];
-        at.once(y, ym);
-        return group_sum<L>(at.squares(ym));
-    };
-
     const float lam = a.lambda;
     if (a.rhs) {
         at.load(a.rhs + (size_t)line * r, res);
@@ -305,27 +344,12 @@ __global__ __launch_bounds__(kBlock, 2) void cg_resident_kernel(CgArgs a)
         res[e] -= fmadd(lam, x[e], q[e]);
         p[e] = res[e];
     }
-    float rr = square(res);
+    float rr = at.square(res);
     for (int it = 0; it < a.iters; ++it) {
         gather(std::true_type{}, p, nullptr, q);
-#pragma unroll
-        for (int e = 0; e < E; ++e) q[e] = fmadd(lam, p[e], q[e]);
-        const float pq = dot(p, q);
-        const float alpha = (rr > 0.f && pq > 0.f) ? rr / pq : 0.f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            x[e] = fmadd(alpha, p[e], x[e]);
-            res[e] = fmadd(-alpha, q[e], res[e]);
-        }
-        const float rrn = square(res);
-        const float beta = rr > 0.f ? rrn / rr : 0.f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) p[e] = fmadd(beta, p[e], res[e]);
-        rr = rrn;
+        rr = cg_step(at, lam, rr, p, q, x, res);
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-        if (at.act[v]) st_row<VW>(Xrow + at.off[v], x + v * VW);
+    at.store(Xrow, x);
 }
 
 // Split lines keep a pass per iteration, which spreads a long line over the chip: a group
@@ -415,115 +439,64 @@ __global__ __launch_bounds__(kBlock) void cg_chunk_sum_kernel(const int32_t *__r
     chunk_sum<1>(splits + 3 * s, r, k, partial, out + (size_t)splits[3 * s] * r + k);
 }
 
-// Start of CG: R = rhs - (Q + lambda X) with Q = (sum_j F_j F_j^T) X from the chunks' partials,
-// P = R, rr = <R, R>.
-// rhs may be R itself.
-template <int L, int NV, int VW>
-__global__ __launch_bounds__(kBlock) void cg_start_kernel(const int32_t *__restrict__ splits, int32_t n_splits,
-                                                          int32_t r, const float *rhs, const float *__restrict__ partial,
-                                                          const float *__restrict__ X, float lambda, float *R,
-                                                          float *__restrict__ P, float *__restrict__ rr)
+// Q = (sum_j F_j F_j^T) y for the line of split s, from its chunks' partials.
+template <class TF, int L, int NV, int VW, bool RAG>
+__device__ __forceinline__ void chunk_sums(const LaneRow<TF, L, NV, VW, RAG> &at, const int32_t *__restrict__ split,
+                                           int32_t r, const float *__restrict__ partial, float *q)
 {
-    const int lane = threadIdx.x % L;
-    const int64_t k = (int64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
-    if (k >= n_splits) return;
-    const int64_t row = splits[3 * k];
-    const int C = r / VW;
-    float dot = 0.f;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int c = v * L + lane;
-        if (c >= C) continue;
-        const int64_t o = row * r + c * VW;
-        float b[VW], q[VW], x[VW], res[VW];
-        ld_row<VW>(rhs + o, b);
-        chunk_sum<VW>(splits + 3 * k, r, c * VW, partial, q);
-        ld_row<VW>(X + o, x);
+        chunk_sum<VW>(split, r, at.off[v], partial, q + v * VW);
 #pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            res[e] = b[e] - (q[e] + lambda * x[e]);
-            dot += res[e] * res[e];
-        }
-        st_row<VW>(R + o, res);
-        st_row<VW>(P + o, res);
+        for (int e = 0; e < VW; ++e) q[v * VW + e] = at.act[v] ? q[v * VW + e] : 0.f;
     }
-    dot = group_sum<L>(dot);
-    if (lane == 0) rr[row] = dot;
 }
 
-// One CG step, with Q = (sum_j F_j F_j^T) P from the chunks' partials:
+// Start of CG: R = rhs - (Q + lambda X), P = R, rr = <R, R>.  rhs may be R itself.
+template <class TF, int L, int NV, int VW, bool RAG>
+__global__ __launch_bounds__(kBlock) void cg_start_kernel(SplitCg a)
+{
+    constexpr int E = NV * VW;
+    const int64_t k = (int64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
+    if (k >= a.n_splits) return;
+    const LaneRow<TF, L, NV, VW, RAG> at(threadIdx.x % L, a.r);
+    const int32_t line = a.splits[3 * k];
+    const size_t row = (size_t)line * a.r;
+    float x[E], q[E], res[E];
+    at.load(a.rhs + row, res);
+    at.load(a.X + row, x);
+    chunk_sums(at, a.splits + 3 * k, a.r, a.partial, q);
+#pragma unroll
+    for (int e = 0; e < E; ++e) res[e] -= fmadd(a.lambda, x[e], q[e]);
+    const float rr = at.square(res);
+    at.store(a.R + row, res);
+    at.store(a.P + row, res);
+    if (threadIdx.x % L == 0) a.rr[line] = rr;
+}
+
+// One CG step, with Q = (sum_j F_j F_j^T) P:
 //   alpha = rr / <P, Q + lambda P>;  X += alpha P;  R -= alpha (Q + lambda P);
 //   beta = <R, R>_new / rr;  P = R + beta P;  rr = <R, R>_new.
 // A line whose residual or curvature is zero keeps its iterate (alpha = beta = 0).
-template <int L, int NV, int VW>
-__global__ __launch_bounds__(kBlock) void cg_step_kernel(const int32_t *__restrict__ splits, int32_t n_splits,
-                                                         int32_t r, float lambda, float *__restrict__ X,
-                                                         float *__restrict__ R, float *__restrict__ P,
-                                                         const float *__restrict__ partial, float *__restrict__ rr)
+template <class TF, int L, int NV, int VW, bool RAG>
+__global__ __launch_bounds__(kBlock) void cg_step_kernel(SplitCg a)
 {
     constexpr int E = NV * VW;
-    const int lane = threadIdx.x % L;
     const int64_t k = (int64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
-    if (k >= n_splits) return;
-    const int64_t row = splits[3 * k];
-    const int C = r / VW;
-    float p[E], mq[E];
-    float pq = 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int c = v * L + lane;
-        float q[VW];
-        if (c < C) {
-            ld_row<VW>(P + row * r + c * VW, p + v * VW);
-            chunk_sum<VW>(splits + 3 * k, r, c * VW, partial, q);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VW; ++e) p[v * VW + e] = q[e] = 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            mq[v * VW + e] = q[e] + lambda * p[v * VW + e];
-            pq += p[v * VW + e] * mq[v * VW + e];
-        }
-    }
-    pq = group_sum<L>(pq);
-    const float rr_old = rr[row];
-    const float alpha = (rr_old > 0.f && pq > 0.f) ? rr_old / pq : 0.f;
-    float res[E];
-    float rrn = 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int c = v * L + lane;
-        if (c >= C) {
-#pragma unroll
-            for (int e = 0; e < VW; ++e) res[v * VW + e] = 0.f;
-            continue;
-        }
-        const int64_t o = row * r + c * VW;
-        float x[VW], rv[VW];
-        ld_row<VW>(X + o, x);
-        ld_row<VW>(R + o, rv);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            x[e] += alpha * p[v * VW + e];
-            res[v * VW + e] = rv[e] - alpha * mq[v * VW + e];
-            rrn += res[v * VW + e] * res[v * VW + e];
-        }
-        st_row<VW>(X + o, x);
-        st_row<VW>(R + o, res + v * VW);
-    }
-    rrn = group_sum<L>(rrn);
-    const float beta = rr_old > 0.f ? rrn / rr_old : 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int c = v * L + lane;
-        if (c >= C) continue;
-        float np[VW];
-#pragma unroll
-        for (int e = 0; e < VW; ++e) np[e] = res[v * VW + e] + beta * p[v * VW + e];
-        st_row<VW>(P + row * r + c * VW, np);
-    }
-    if (lane == 0) rr[row] = rrn;
+    if (k >= a.n_splits) return;
+    const LaneRow<TF, L, NV, VW, RAG> at(threadIdx.x % L, a.r);
+    const int32_t line = a.splits[3 * k];
+    const size_t row = (size_t)line * a.r;
+    float p[E], q[E], x[E], res[E];
+    at.load(a.P + row, p);
+    at.load(a.X + row, x);
+    at.load(a.R + row, res);
+    chunk_sums(at, a.splits + 3 * k, a.r, a.partial, q);
+    const float rr = cg_step(at, a.lambda, a.rr[line], p, q, x, res);
+    at.store(a.X + row, x);
+    at.store(a.R + row, res);
+    at.store(a.P + row, p);
+    if (threadIdx.x % L == 0) a.rr[line] = rr;
 }
 
 // Per-block partial sums of (val[p] - R[p])^2 in float64, then one block adds the
@@ -592,85 +565,66 @@ hipError_t launch_chunks(const fmm_sparse *S, const void *F, int32_t r, const fl
 }
 
 // Lanes per row by the number of vectors in a row.
-template <class TF, int VW, class Fn> hipError_t by_width(int r, Fn fn)
+template <class TF, int VW, bool RAG, class Fn> hipError_t by_width(int r, Fn fn)
 {
     const int C = (r + VW - 1) / VW;
 #define CG_WIDTH(Lv, NVv) fn(std::integral_constant<int, Lv>{}, std::integral_constant<int, NVv>{})
-    if (VW == 1 || C <= 4) return CG_WIDTH(4, 1);  // VW = 1: r < 4
-    if constexpr (VW > 1) {
+    if (C <= 4) return CG_WIDTH(4, 1);
+    if constexpr (VW == 1) {  // r < 4 or over 64
+        if (C <= 128) return CG_WIDTH(64, 2);
+        return CG_WIDTH(64, 4);
+    } else {
         if (C <= 8) return CG_WIDTH(8, 1);
         if (C <= 16) return CG_WIDTH(16, 1);
-        if (C <= 32) return CG_WIDTH(32, 1);
-        if (C <= 64) return CG_WIDTH(64, 1);
-        if (C <= 128) return CG_WIDTH(64, 2);
+        if constexpr (!RAG) {  // r of up to 64
+            if (C <= 32) return CG_WIDTH(32, 1);
+            if (C <= 64) return CG_WIDTH(64, 1);
+            if (C <= 128) return CG_WIDTH(64, 2);
+            if constexpr (VW == 4) return CG_WIDTH(64, 4);
+        }
     }
-    if constexpr (VW == 4) return CG_WIDTH(64, 4);
 #undef CG_WIDTH
     return hipErrorInvalidValue;
 }
 
+// The form of a row for every kernel here: fn with its type, vector and overlap, then its lanes.
+// Above 64 elements a row of no whole vectors goes by elements, 64 apart in a lane.
+template <class Fn> hipError_t by_row(int32_t dtype, int r, Fn fn)
+{
+    auto with = [&](auto tf, auto vw, auto rag) {
+        return by_width<decltype(tf), decltype(vw)::value, decltype(rag)::value>(r, [&](auto L, auto NV) { return fn(tf, L, NV, vw, rag); });
+    };
+    typedef std::integral_constant<int, 1> V1;
+    typedef std::integral_constant<int, 4> V4;
+    if (dtype == FMM_BF16) return with(bf16_t(), std::integral_constant<int, 8>{}, std::false_type{});
+    if (r % 4 == 0) return with(float(), V4{}, std::false_type{});
+    if (r < 4 || r > 64) return with(float(), V1{}, std::false_type{});
+    return with(float(), V4{}, std::true_type{});
+}
+
 // Slots that fill the registers of two waves per SIMD beside the line's four or five vectors.
-template <class TF, int VW, bool RAG> hipError_t resident_lines(const CgArgs &a, hipStream_t st)
+hipError_t resident_lines(int32_t dtype, const CgArgs &a, hipStream_t st)
 {
-    return by_width<TF, VW>(a.r, [&](auto L, auto NV) {
-        constexpr int l = L.value, nv = NV.value;
-        if constexpr (nv == 1) return launch_resident<TF, l, nv, VW, RAG, 40, VW == 8 ? 4 : 8>(a, st);
-        else if constexpr (nv == 2) return launch_resident<TF, l, nv, VW, RAG, VW == 8 ? 12 : 18, 2>(a, st);
-        else return launch_resident<TF, l, nv, VW, RAG, 4, 2>(a, st);
+    return by_row(dtype, a.r, [&](auto tf, auto L, auto NV, auto VW, auto RAG) {
+        typedef decltype(tf) TF;
+        constexpr int l = L.value, nv = NV.value, vw = VW.value;
+        constexpr bool rag = RAG.value;
+        if constexpr (nv == 1) return launch_resident<TF, l, nv, vw, rag, 40, vw == 8 ? 4 : 8>(a, st);
+        else if constexpr (vw == 1) return launch_resident<TF, l, nv, vw, rag, nv == 2 ? 72 : 36, nv == 2 ? 8 : 4>(a, st);
+        else if constexpr (nv == 2) return launch_resident<TF, l, nv, vw, rag, vw == 8 ? 12 : 18, 2>(a, st);
+        else return launch_resident<TF, l, nv, vw, rag, 4, 2>(a, st);
     });
 }
 
-template <class TF, int VW, bool RAG>
-hipError_t chunk_partials(const fmm_sparse *S, const void *F, int32_t r, const float *H, void *ws, hipStream_t st)
-{
-    return by_width<TF, VW>(r, [&](auto L, auto NV) {
-        return launch_chunks<TF, L.value, NV.value, VW, RAG>(S, F, r, H, ws, st);
-    });
-}
-
-hipError_t split_partials(const fmm_sparse *S, const void *F, int32_t r, int32_t dtype, const float *H, void *ws,
-                          hipStream_t st)
-{
-    if (dtype == FMM_BF16) return chunk_partials<bf16_t, 8, false>(S, F, r, H, ws, st);
-    if (r < 4) return chunk_partials<float, 1, false>(S, F, r, H, ws, st);
-    return r % 4 ? chunk_partials<float, 4, true>(S, F, r, H, ws, st)
-                 : chunk_partials<float, 4, false>(S, F, r, H, ws, st);
-}
-
-struct SplitCg {
-    const int32_t *splits;
-    int32_t n_splits, r;
-    float lambda;
-    float *X, *R, *P, *rr;
-    const float *partial;
-};
-
-template <int L, int NV, int VW>
-hipError_t launch_split_cg(const SplitCg &c, const float *start_rhs, hipStream_t st)
+// begin: the start of the iteration; else one step.
+template <class TF, int L, int NV, int VW, bool RAG>
+hipError_t launch_split_cg(const SplitCg &c, bool begin, hipStream_t st)
 {
     const unsigned nb = (unsigned)(((int64_t)c.n_splits + kBlock / L - 1) / (kBlock / L));
     if (nb == 0) return hipSuccess;
-    if (start_rhs)
-        hipLaunchKernelGGL((cg_start_kernel<L, NV, VW>), dim3(nb), dim3(kBlock), 0, st, c.splits, c.n_splits, c.r,
-                           start_rhs, c.partial, (const float *)c.X, c.lambda, c.R, c.P, c.rr);
-    else
-        hipLaunchKernelGGL((cg_step_kernel<L, NV, VW>), dim3(nb), dim3(kBlock), 0, st, c.splits, c.n_splits, c.r,
-                           c.lambda, c.X, c.R, c.P, c.partial, c.rr);
+    if (begin) hipLaunchKernelGGL((cg_start_kernel<TF, L, NV, VW, RAG>), dim3(nb), dim3(kBlock), 0, st, c);
+    else hipLaunchKernelGGL((cg_step_kernel<TF, L, NV, VW, RAG>), dim3(nb), dim3(kBlock), 0, st, c);
     return hipGetLastError();
-}
-
-// start_rhs: begin the iteration from this right-hand side; NULL: one step.
-hipError_t split_cg(const SplitCg &c, const float *start_rhs, hipStream_t st)
-{
-    const int vw = c.r % 4 == 0 ? 4 : 1;
-    const Shape sh = default_shape(c.r, vw);
-#define CG_CASE(Lv, NVv)                                                                         \
-    if (sh.L == Lv && sh.NV == NVv)                                                              \
-        return vw == 4 ? launch_split_cg<Lv, NVv, 4>(c, start_rhs, st) : launch_split_cg<Lv, NVv, 1>(c, start_rhs, st);
-    CG_CASE(1, 1) CG_CASE(2, 1) CG_CASE(4, 1) CG_CASE(8, 1) CG_CASE(16, 1) CG_CASE(32, 1) CG_CASE(64, 1)
-    CG_CASE(64, 2) CG_CASE(64, 4)
-#undef CG_CASE
-    return hipErrorInvalidValue;
 }
 
 // CG for every line of S: those of up to long_len entries in one kernel, the split ones by
@@ -722,8 +676,14 @@ fmm_status solve_lines(const fmm_sparse *S, const void *F, int32_t r, int32_t dt
         c.P = work + (size_t)n * r;
         c.partial = static_cast<const float *>(ws);
         c.rr = work + 3 * (size_t)n * r;
+        c.rhs = rhs ? rhs : c.R;
+        auto partials = [&](const float *H) {  // of <H_line, F_j> F_j, or for NULL of val_p F_j
+            return by_row(dtype, r, [&](auto tf, auto L, auto NV, auto VW, auto RAG) {
+                return launch_chunks<decltype(tf), L.value, NV.value, VW.value, RAG.value>(S, F, r, H, ws, stream);
+            });
+        };
         if (!rhs) {
-            e = split_partials(S, F, r, dtype, nullptr, ws, stream);
+            e = partials(nullptr);
             if (e != hipSuccess) return hipfail(e);
             const int64_t nb = ((int64_t)S->n_splits * r + kBlock - 1) / kBlock;
             if (nb > 0x7fffffffLL) return hipfail(hipErrorInvalidConfiguration);
@@ -735,16 +695,15 @@ fmm_status solve_lines(const fmm_sparse *S, const void *F, int32_t r, int32_t dt
             }
         }
         for (int32_t it = -1; it < iters; ++it) {
-            e = split_partials(S, F, r, dtype, it < 0 ? X : c.P, ws, stream);
+            e = partials(it < 0 ? X : c.P);
             if (e != hipSuccess) return hipfail(e);
-            e = split_cg(c, it < 0 ? (rhs ? rhs : c.R) : nullptr, stream);
+            e = by_row(dtype, r, [&](auto tf, auto L, auto NV, auto VW, auto RAG) {
+                return launch_split_cg<decltype(tf), L.value, NV.value, VW.value, RAG.value>(c, it < 0, stream);
+            });
             if (e != hipSuccess) return hipfail(e);
         }
     }
-    if (dtype == FMM_BF16) e = resident_lines<bf16_t, 8, false>(a, stream);
-    else if (r < 4) e = resident_lines<float, 1, false>(a, stream);
-    else if (r % 4) e = resident_lines<float, 4, true>(a, stream);
-    else e = resident_lines<float, 4, false>(a, stream);
+    e = resident_lines(dtype, a, stream);
     return e == hipSuccess ? FMM_OK : hipfail(e);
 }
 
