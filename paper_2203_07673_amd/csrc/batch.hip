@@ -51,22 +51,39 @@ fmm_status hipfail(hipError_t e)
         if (_e != hipSuccess) return hipfail(_e);                                                \
     } while (0)
 
+// Whether the forward and dA rows of a tile go in one pass (PASS_ROWS), for plans that compute
+// both: from 2^17 entries on.  A smaller launch leaves workgroups idle, which separate tiles
+// can have.  Separate / one pass in us, tuned: 87 thousand entries, r = 80, bfloat16 42.9 / 43.6,
+// 117 thousand, r = 88 48.0 / 50.1, 97 thousand, r = 120 55.5 / 56.1; 165 thousand, r = 32, float32
+// 19.4 / 18.2, 153 thousand, r = 48, bfloat16 33.9 / 31.8, 367 thousand, r = 16, float32 18.2 / 16.1;
+// the mean of 19 plans below 2^17 entries is the same, of 9 up to 2^18 3% apart, of 38 above 8%.
+constexpr int64_t kOneRowPassEntries = 1 << 17;
+bool one_row_pass(const fmm_batch_plan *p)
+{
+    if (!(p->flags & FMM_BATCH_FWD) || !(p->flags & FMM_BATCH_BWD)) return false;
+    int64_t entries = 0;
+    for (const std::vector<int32_t> &ptr : p->rowptr) entries += ptr.back();
+    return entries >= kOneRowPassEntries;
+}
+
 BatchKernelFn kernel_for(const fmm_batch_plan *p, int rw, int cw)
 {
+    const bool rows = one_row_pass(p);
     if (p->dtype == FMM_BF16) {
-        if (p->flags & FMM_BATCH_DC_BF16) return batch_kernel_for<bf16_t, bf16_t>(p->L, rw, cw);
-        return batch_kernel_for<bf16_t, float>(p->L, rw, cw);
+        if (p->flags & FMM_BATCH_DC_BF16) return batch_kernel_for<bf16_t, bf16_t>(p->L, rw, cw, rows);
+        return batch_kernel_for<bf16_t, float>(p->L, rw, cw, rows);
     }
-    return batch_kernel_for<float, float>(p->L, rw, cw);
+    return batch_kernel_for<float, float>(p->L, rw, cw, rows);
 }
 
 BatchQueueKernelFn queue_kernel_for(const fmm_batch_plan *p, int rw, int cw)
 {
+    const bool rows = one_row_pass(p);
     if (p->dtype == FMM_BF16) {
-        if (p->flags & FMM_BATCH_DC_BF16) return batch_queue_kernel_for<bf16_t, bf16_t>(p->L, rw, cw);
-        return batch_queue_kernel_for<bf16_t, float>(p->L, rw, cw);
+        if (p->flags & FMM_BATCH_DC_BF16) return batch_queue_kernel_for<bf16_t, bf16_t>(p->L, rw, cw, rows);
+        return batch_queue_kernel_for<bf16_t, float>(p->L, rw, cw, rows);
     }
-    return batch_queue_kernel_for<float, float>(p->L, rw, cw);
+    return batch_queue_kernel_for<float, float>(p->L, rw, cw, rows);
 }
 
 // Kernel of a schedule, for occupancy queries.
@@ -87,14 +104,14 @@ void cut_tiles(const fmm_batch_plan *p, int32_t tile_nnz, std::vector<std::vecto
 {
     const double e = p->ebytes, r = p->r;
     const double ed = (p->flags & FMM_BATCH_DC_BF16) ? 2 : 4;  // bytes per element of dC
+    const bool rows = one_row_pass(p);
     per_graph->assign(p->nbatch, {});
     for (int32_t g = 0; g < p->nbatch; ++g) {
-        const bool fwd = (p->flags & FMM_BATCH_FWD) != 0, bwd = (p->flags & FMM_BATCH_BWD) != 0;
         for (int pass : {PASS_FWD, PASS_BWD_ROW, PASS_ROWS, PASS_BWD_COL}) {
-            if (pass == PASS_FWD && !(fwd && !bwd)) continue;
-            if (pass == PASS_BWD_ROW && !(bwd && !fwd)) continue;
-            if (pass == PASS_ROWS && !(fwd && bwd)) continue;
-            if (pass == PASS_BWD_COL && !bwd) continue;
+            if (pass == PASS_FWD && (rows || !(p->flags & FMM_BATCH_FWD))) continue;
+            if (pass == PASS_BWD_ROW && (rows || !(p->flags & FMM_BATCH_BWD))) continue;
+            if (pass == PASS_ROWS && !rows) continue;
+            if (pass == PASS_BWD_COL && !(p->flags & FMM_BATCH_BWD)) continue;
             const std::vector<int32_t> &ptr = pass == PASS_BWD_COL ? p->colptr[g] : p->rowptr[g];
             const int32_t nl = (int32_t)ptr.size() - 1;
             const double per_entry = pass == PASS_BWD_COL ? (e + ed) * r + 8 : e * r + 8;
@@ -187,8 +204,8 @@ void place_tiles(const fmm_batch_plan *p, const std::vector<std::vector<TileCost
 }
 
 // Queues: one per XCD, holding its graphs (largest first) one after another.  Inside a
-// graph the row tiles come first, then the dB tiles.  qoff[q] .. qoff[q + 1] - 1 are queue
-// q's.
+// graph the row tiles come first, the forward and dA tiles of a line range side by side (both
+// gather the same rows of B), then the dB tiles.  qoff[q] .. qoff[q + 1] - 1 are queue q's.
 void queue_tiles(const fmm_batch_plan *p, const std::vector<std::vector<TileCost>> &per_graph,
                  std::vector<BatchTile> *tiles, std::vector<int32_t> *qoff)
 {
@@ -199,9 +216,13 @@ void queue_tiles(const fmm_batch_plan *p, const std::vector<std::vector<TileCost
     for (int q = 0; q < nq; ++q) {
         (*qoff)[q] = (int32_t)tiles->size();
         for (int32_t g : xgraphs[q]) {
-            for (bool col : {false, true})
-                for (const TileCost &t : per_graph[g])
-                    if ((t.t.pass == PASS_BWD_COL) == col) tiles->push_back(t.t);
+            std::vector<BatchTile> rowp, colp;
+            for (const TileCost &t : per_graph[g]) (t.t.pass == PASS_BWD_COL ? colp : rowp).push_back(t.t);
+            std::stable_sort(rowp.begin(), rowp.end(), [](const BatchTile &a, const BatchTile &b) {
+                return a.l0 != b.l0 ? a.l0 < b.l0 : a.pass < b.pass;
+            });
+            tiles->insert(tiles->end(), rowp.begin(), rowp.end());
+            tiles->insert(tiles->end(), colp.begin(), colp.end());
         }
     }
     (*qoff)[nq] = (int32_t)tiles->size();

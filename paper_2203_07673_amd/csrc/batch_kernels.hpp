@@ -38,7 +38,7 @@ constexpr int batch_blocks_per_cu(int gpl_c) { return gpl_c > 1 ? 5 : 4; }
 
 // The lines of one tile, with the entry operands read through idx and val at positions
 // relative to `base` (the tile's first entry when they are staged in LDS, else 0).
-template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C>
+template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C, bool ROWS>
 __device__ __forceinline__ void run_lines(const BatchGraphDev &g, const BatchTile &tl, int32_t r,
                                           const int32_t *idx, const float *val, int32_t base)
 {
@@ -68,19 +68,19 @@ __device__ __forceinline__ void run_lines(const BatchGraphDev &g, const BatchTil
         o.G2 = g.B;
         for (int32_t line = tl.l0 + slot; line < tl.l1; line += LPB) {
             const int32_t b = g.rowptr[line] - base, e = g.rowptr[line + 1] - base;
-            if (tl.pass == PASS_ROWS) {
+            if constexpr (ROWS) {
                 o.H = g.A;
                 o.H2 = g.dC;
                 o.out2 = g.dA;
-                process_line<OP_FUSED1D, TS, TS, TD, float, L, 1, VW, UD, GPL_R, false>(
+                process_line<OP_FUSED1D, TS, TS, TD, float, L, 1, VW, UD, GPL_R, false, false, false>(
                     o, lane, gidx, line, b, e, g.C + (size_t)line * r, false);
             } else if (tl.pass == PASS_FWD) {
                 o.H = g.A;
-                process_line<OP_FUSED1, TS, TS, TS, float, L, 1, VW, UR, GPL_R, false>(
+                process_line<OP_FUSED1, TS, TS, TS, float, L, 1, VW, UR, GPL_R, false, false, false>(
                     o, lane, gidx, line, b, e, g.C + (size_t)line * r, false);
             } else {
                 o.H = g.dC;
-                process_line<OP_FUSED1, TD, TS, TS, float, L, 1, VW, UR, GPL_R, false>(
+                process_line<OP_FUSED1, TD, TS, TS, float, L, 1, VW, UR, GPL_R, false, false, false>(
                     o, lane, gidx, line, b, e, g.dA + (size_t)line * r, false);
             }
         }
@@ -94,7 +94,7 @@ __device__ __forceinline__ void run_lines(const BatchGraphDev &g, const BatchTil
         o.G2 = g.dC;
         for (int32_t line = tl.l0 + slot; line < tl.l1; line += LPB) {
             const int32_t b = g.colptr[line] - base, e = g.colptr[line + 1] - base;
-            process_line<OP_FUSED2, TS, TS, TD, float, L, 1, VW, UC, GPL_C, false>(
+            process_line<OP_FUSED2, TS, TS, TD, float, L, 1, VW, UC, GPL_C, false, false, false>(
                 o, lane, gidx, line, b, e, g.dB + (size_t)line * r, false);
         }
     }
@@ -110,7 +110,7 @@ __device__ __forceinline__ void run_lines(const BatchGraphDev &g, const BatchTil
 // batch of U entries reads its operands from LDS instead of waiting on a memory round
 // trip before it can issue its row loads; the lines then run on entry positions
 // relative to the tile.  The caller separates tiles with a barrier.
-template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C>
+template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C, bool ROWS>
 __device__ __forceinline__ void run_tile(const BatchGraphDev *__restrict__ graphs, const BatchTile &tl, int32_t r,
                                          int32_t *s_idx, float *s_val)
 {
@@ -126,14 +126,14 @@ __device__ __forceinline__ void run_tile(const BatchGraphDev *__restrict__ graph
             s_val[k] = gval ? gval[first + k] : 1.0f;
         }
         __syncthreads();
-        run_lines<TS, TD, L, VW, GPL_R, GPL_C>(g, tl, r, s_idx, s_val, first);
+        run_lines<TS, TD, L, VW, GPL_R, GPL_C, ROWS>(g, tl, r, s_idx, s_val, first);
     } else {
-        run_lines<TS, TD, L, VW, GPL_R, GPL_C>(g, tl, r, gidx, gval, 0);
+        run_lines<TS, TD, L, VW, GPL_R, GPL_C, ROWS>(g, tl, r, gidx, gval, 0);
     }
 }
 
 // Static placement: workgroup w runs tiles wg_off[w] .. wg_off[w + 1] - 1 in order.
-template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C>
+template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C, bool ROWS>
 __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_kernel(const BatchGraphDev *__restrict__ graphs,
                                                        const BatchTile *__restrict__ tiles,
                                                        const int32_t *__restrict__ wg_off, int32_t r)
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_kern
     __shared__ float s_val[kStageEntries];
     const int32_t t0 = wg_off[blockIdx.x], t1 = wg_off[blockIdx.x + 1];
     for (int32_t t = t0; t < t1; ++t) {
-        run_tile<TS, TD, L, VW, GPL_R, GPL_C>(graphs, tiles[t], r, s_idx, s_val);
+        run_tile<TS, TD, L, VW, GPL_R, GPL_C, ROWS>(graphs, tiles[t], r, s_idx, s_val);
         __syncthreads();  // the staged operands are overwritten by the next tile
     }
 }
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_kern
 // queue's end fails without effect, so each workgroup stops after at most one failed
 // claim per queue; the last workgroup to finish (counted in next[n_q]) puts the counters
 // back to zero for the next launch.  Launches of one plan must not overlap in time.
-template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C>
+template <class TS, class TD, int L, int VW, int GPL_R, int GPL_C, bool ROWS>
 __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_queue_kernel(const BatchGraphDev *__restrict__ graphs,
                                                              const BatchTile *__restrict__ tiles,
                                                              const int32_t *__restrict__ q_off, int32_t *next,
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_queu
             __syncthreads();  // every wave has read the claim before the next one overwrites it
             if (t < 0) break;
             // the barriers above also keep a new tile's staging after the last tile's reads
-            run_tile<TS, TD, L, VW, GPL_R, GPL_C>(graphs, tiles[t], r, s_idx, s_val);
+            run_tile<TS, TD, L, VW, GPL_R, GPL_C, ROWS>(graphs, tiles[t], r, s_idx, s_val);
         }
     }
     if (threadIdx.x == 0) {
@@ -189,12 +189,13 @@ __global__ __launch_bounds__(kBlock, batch_blocks_per_cu(GPL_C)) void batch_queu
     }
 }
 
-// Host-side launcher tables for one storage type: (L, row schedule, column schedule).
+// Host-side launcher tables for one storage type: (L, row schedule, column schedule), and whether
+// the row tiles are PASS_ROWS or the separate passes.
 typedef void (*BatchKernelFn)(const BatchGraphDev *, const BatchTile *, const int32_t *, int32_t);
 typedef void (*BatchQueueKernelFn)(const BatchGraphDev *, const BatchTile *, const int32_t *, int32_t *, int32_t,
                                    int32_t);
 
-template <class TS, class TD> BatchKernelFn batch_kernel_for(int L, int row_wave, int col_wave);
-template <class TS, class TD> BatchQueueKernelFn batch_queue_kernel_for(int L, int row_wave, int col_wave);
+template <class TS, class TD> BatchKernelFn batch_kernel_for(int L, int row_wave, int col_wave, bool rows);
+template <class TS, class TD> BatchQueueKernelFn batch_queue_kernel_for(int L, int row_wave, int col_wave, bool rows);
 
 }  // namespace fmm

@@ -578,8 +578,9 @@ struct LineOperands {
 // line (GPL > 1: wavefront-per-line; group gidx takes every GPL-th batch of U entries
 // and the partial sums are added across groups at the end).  dst receives the line's
 // r-vector (beta applied when keep_beta); OP_SDDMM writes per-entry values instead.
+// RAG: r may be no multiple of VW.
 template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U, int GPL, bool PF = true,
-          bool HINT = false>
+          bool HINT = false, bool RAG = VW == 2 || VW == 4>
 __device__ __forceinline__ void process_line(const LineOperands &o, int lane, int gidx, int32_t line, int32_t begin,
                                              int32_t end, Acc *dst, bool keep_beta)
 {
@@ -587,10 +588,10 @@ __device__ __forceinline__ void process_line(const LineOperands &o, int lane, in
     const int r = o.r;
 
     // vectors this lane owns inside an r-vector
-    const bool ragged = VW > 1 && r % VW != 0;
-    RowVec<VW> rv[NV];
+    const bool ragged = RAG && r % VW != 0;
+    RowVec<VW, RAG> rv[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) rv[v] = RowVec<VW>(v * L + lane, r);
+    for (int v = 0; v < NV; ++v) rv[v] = RowVec<VW, RAG>(v * L + lane, r);
 
     const int32_t *__restrict__ idx = o.idx;
     const Acc *__restrict__ val = static_cast<const Acc *>(o.val);
