@@ -647,7 +647,7 @@ fmm_status solve_lines(const fmm_sparse *S, const void *F, int32_t r, int32_t dt
     const int vw = r % 4 == 0 ? 4 : 1;
     if (r > 64 * 4 * vw) return FMM_ERR_DTYPE;
     if (vw == 4 && ((uintptr_t)rhs % 16 || (uintptr_t)X % 16 || (uintptr_t)work % 16)) return FMM_ERR_UNSUPPORTED;
-    fmm_status s = gram_check(S, r, dtype, ws, ws_bytes);
+    fmm_status s = gram_check(S, F, r, dtype, ws, ws_bytes);
     if (s != FMM_OK) return s;
     CgArgs a;
     memset(&a, 0, sizeof(a));

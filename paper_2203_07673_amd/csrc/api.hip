@@ -260,11 +260,18 @@ fmm_status values_unfused(const fmm_sparse *S_csr, const Kinds &k, const void *A
 // ---------------------------------------------------------------- internal helpers
 
 namespace fmm {
-fmm_status gram_check(const fmm_sparse *S, int32_t r, int32_t dtype, void *ws, size_t ws_bytes)
+fmm_status gram_check(const fmm_sparse *S, const void *F, int32_t r, int32_t dtype, void *ws, size_t ws_bytes)
 {
     Kinds k;
     FMM_TRY(kinds_for(dtype, r, &k));
     if (k.path == PATH_F64) return FMM_ERR_DTYPE;
+    if (nmajor(S) > 0) {  // without lines nothing is read
+        fmm_sparse pat = *S;
+        pat.variant = FMM_VARIANT_AUTO;  // not used by the solve
+        FMM_TRY(check_sparse(&pat, -1));
+        // float32 rows are read at any element
+        if (dtype == FMM_BF16) FMM_TRY(check_dense(F, nminor(S), k.sbytes, r));
+    }
     return check_ws(S, r, k.obytes, ws, ws_bytes);
 }
 }  // namespace fmm

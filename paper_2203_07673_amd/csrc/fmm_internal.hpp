@@ -93,8 +93,8 @@ template <int OP, class TH, class TG1, class TG2, class Acc>
 hipError_t launch_lines(const LineArgs &a, int32_t n_splits, const int32_t *splits, Shape hint,
                         hipStream_t stream);
 
-// The argument checks of the batched CG that its pattern and workspace need (api.hip).
-fmm_status gram_check(const fmm_sparse *S, int32_t r, int32_t dtype, void *ws, size_t ws_bytes);
+// The argument checks of the batched CG on its pattern, gathered rows and split workspace (api.hip).
+fmm_status gram_check(const fmm_sparse *S, const void *F, int32_t r, int32_t dtype, void *ws, size_t ws_bytes);
 
 // Pattern preparation kernels (pattern.hip).
 size_t transpose_workspace_bytes(int64_t m, int64_t n, int64_t nnz);
