@@ -17,6 +17,7 @@ from __future__ import annotations
 
 import copy
 import ctypes
+import threading
 from typing import Optional
 
 import numpy as np
@@ -36,6 +37,7 @@ SPLIT_CANDIDATES = (256, 128, 64)
 # many bytes of gathered rows hold (the L2 of the 8 XCDs together: 32 MiB).
 HINT_BYTES = 32 << 20
 _NO_SPLIT = (1 << 31) - 1
+SCRATCH_KEPT = 16  # workspaces that a pattern keeps, over sizes, streams and threads
 
 
 def _stream():
@@ -125,6 +127,7 @@ class Pattern:
         C.load()
         self.device = device
         self.m, self.n = int(shape[0]), int(shape[1])
+        self._many_lines = max(self.m, self.n) >= 1 << 18
         self.rowptr = _dev_tensor(rowptr, torch.int32, device)
         self.colidx = _dev_tensor(colidx, torch.int32, device)
         self.val = _dev_tensor(val, val_dtype, device) if val is not None else None
@@ -338,7 +341,7 @@ class Pattern:
         gains above 2^20 lines, r = 128 915 / 871, bfloat16 r = 256 3535 / 3267; the one-row pass
         does not (2340 / 2430)."""
         d = self.csr if orient == C.FMM_CSR else self.csc
-        if not d.order or self._order_chosen[orient] or X.dtype == torch.float64:
+        if not self._many_lines or not d.order or self._order_chosen[orient] or X.dtype == torch.float64:
             return d
         lines = self.m if orient == C.FMM_CSR else self.n
         row = X.shape[1] * X.element_size()
@@ -508,7 +511,7 @@ class Pattern:
         return {"csr": self._csr_sched, "csc": self._csc_sched}
 
     def workspace(self, op: int, r: int, dcode: int):
-        """Device workspace for a call (cached by size); None when not needed."""
+        """Device workspace for a call and its bytes (None, 0 when not needed)."""
         key = (op, r, dcode, self.csr.n_chunks, self.csc.n_chunks)
         size = self._ws_sizes.get(key)
         if size is None:
@@ -516,16 +519,29 @@ class Pattern:
             C.call("fmm_workspace_size", op, ctypes.byref(self.csr), ctypes.byref(self.csc), r, dcode,
                    ctypes.byref(bytes_))
             size = self._ws_sizes[key] = bytes_.value
-        if size == 0:
-            return None, 0
-        ws = self._ws_cache.get(size)
+        return self._scratch(size), size
+
+    def _scratch(self, size, use="partials"):
+        """`size` bytes that calls of one thread on one stream share (their kernels follow one
+        another): kept by both, since calls on two streams, or whose launches two threads mix,
+        would write over each other's partial sums.  Under capture the memory belongs to the
+        graph, whose replays may overlap later calls.  At most SCRATCH_KEPT are kept; the
+        oldest goes back to the allocator, which hands it on in its stream's order."""
+        if not size:
+            return None
+        if torch._C._cuda_isCurrentStreamCapturing():
+            return torch.empty(size, dtype=torch.uint8, device=self.device)
+        key = (use, size, _stream(), threading.get_ident())
+        ws = self._ws_cache.get(key)
         if ws is None:
             ws = torch.empty(size, dtype=torch.uint8, device=self.device)
-            self._ws_cache[size] = ws
-        return ws, size
+            self._ws_cache[key] = ws
+            for old in list(self._ws_cache)[:-SCRATCH_KEPT]:
+                self._ws_cache.pop(old, None)
+        return ws
 
     def _gat_workspace(self, backward, r, dcode):
-        """The attention head's workspace (tensor or None, bytes), kept like the others."""
+        """The same for the attention head."""
         csr, csc = self.csr, self.csc
         key = ("gat_bwd" if backward else "gat", r, dcode, csr.n_chunks, csc.n_chunks, bool(csc.perm))
         size = self._ws_sizes.get(key)
@@ -536,13 +552,7 @@ class Pattern:
             else:
                 C.call("fmm_gat_workspace", ctypes.byref(csr), r, dcode, ctypes.byref(nb))
             size = self._ws_sizes[key] = nb.value
-        if size == 0:
-            return None, 0
-        ws = self._ws_cache.get((key[0], size))
-        if ws is None:
-            ws = torch.empty(size, dtype=torch.uint8, device=self.device)
-            self._ws_cache[(key[0], size)] = ws
-        return ws, size
+        return self._scratch(size), size
 
 
 def _common(P: Pattern, A, B):
@@ -572,7 +582,7 @@ def fusedmm_a_raw(P, A, B, out=None, fused=True, R_ws=None):
     elif R_ws is not None:
         _check_buf("R_ws", R_ws, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A, r, dcode)
-    csr = P._fused_desc(C.FMM_CSR, False, A) if fused else P.csr
+    csr = P._fused_desc(C.FMM_CSR, False, A) if fused and P._many_lines else P.csr
     C.call("fmm_fusedmm_a", ctypes.byref(csr), _ptr(A), _ptr(B), r, dcode, _ptr(out),
            C.FMM_FUSED if fused else C.FMM_UNFUSED, _ptr(R_ws), _ptr(ws), wb, _stream())
     return out, R_ws
@@ -610,7 +620,7 @@ def fusedmm_b_raw(P, A, B, out=None, fused=True, R_ws=None):
     elif R_ws is not None:
         _check_buf("R_ws", R_ws, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_B, r, dcode)
-    csc = P._fused_desc(C.FMM_CSC, False, A) if fused else P.csc
+    csc = P._fused_desc(C.FMM_CSC, False, A) if fused and P._many_lines else P.csc
     C.call("fmm_fusedmm_b", ctypes.byref(csc), _ptr(A), _ptr(B), r, dcode, _ptr(out),
            C.FMM_FUSED if fused else C.FMM_UNFUSED, _ptr(R_ws), _ptr(ws), wb, _stream())
     return out, R_ws
@@ -656,7 +666,7 @@ def _fused_backward(form, P, A, B, dC, dA, dB, need, fused, R_ws, dP_ws, grad16=
             _check_buf(name, buf, P.device, odt, min_numel=P.nnz)
     ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A_BWD if form == "a" else C.FMM_OP_FUSEDMM_B_BWD, r, dcode)
     csr, csc = P.csr, P.csc
-    if fused:  # the one-row pass runs on the form's own orientation, the two-row pass on the other
+    if fused and P._many_lines:  # the one-row pass runs on the form's own orientation, the two-row pass on the other
         csr, csc = P._fused_desc(C.FMM_CSR, form == "b", A), P._fused_desc(C.FMM_CSC, form == "a", A)
     C.call("fmm_fusedmm_a_backward" if form == "a" else "fmm_fusedmm_b_backward", ctypes.byref(csr),
            ctypes.byref(csc), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dA if need[0] else None),
@@ -704,12 +714,12 @@ def _values_backward(form, P, A, B, dC, dS, dX, want_dX, fused, grad16=False):
     flags = (C.FMM_FUSED if fused else C.FMM_UNFUSED) | (C.FMM_GRAD_BF16 if grad16 else 0)
     out = _ptr(dX if want_dX else None)
     if form == "a":
-        csr = P._fused_desc(C.FMM_CSR, False, A) if fused else P.csr
+        csr = P._fused_desc(C.FMM_CSR, False, A) if fused and P._many_lines else P.csr
         ws, wb = P.workspace(C.FMM_OP_FUSEDMM_A_BWD_VALUES, r, dcode)
         C.call("fmm_fusedmm_a_backward_values", ctypes.byref(csr), _ptr(A), _ptr(B), _ptr(dC), r, dcode, _ptr(dS),
                out, flags, _ptr(ws), wb, _stream())
     else:
-        csc = P._fused_desc(C.FMM_CSC, False, A) if fused else P.csc
+        csc = P._fused_desc(C.FMM_CSC, False, A) if fused and P._many_lines else P.csc
         ws, wb = P.workspace(C.FMM_OP_FUSEDMM_B_BWD_VALUES, r, dcode)
         C.call("fmm_fusedmm_b_backward_values", ctypes.byref(P.csr), ctypes.byref(csc), _ptr(A), _ptr(B), _ptr(dC), r,
                dcode, _ptr(dS), out, flags, _ptr(ws), wb, _stream())
@@ -1122,10 +1132,7 @@ def _cg_work(P: Pattern, orient, F, X):
     _check_dense("X", X, nmaj, r, P.device)
     wb = ctypes.c_size_t(0)
     C.call("fmm_cg_work_size", nmaj, r, ctypes.byref(wb))
-    work = P._ws_cache.get(("cg", wb.value))
-    if work is None:
-        work = torch.empty(wb.value // 4, dtype=torch.float32, device=P.device)
-        P._ws_cache[("cg", wb.value)] = work
+    work = P._scratch(wb.value, "cg")
     ws, wsb = P.workspace(C.FMM_OP_FUSEDMM_A if orient == C.FMM_CSR else C.FMM_OP_FUSEDMM_B, r, dcode)
     return P.descriptor(orient), dcode, work, wb.value, ws, wsb
 
@@ -1164,10 +1171,7 @@ def als_residual(P: Pattern, A, B):
         raise TypeError(f"A is {A.dtype} but B is {B.dtype}")
     nb = ctypes.c_size_t(0)
     C.call("fmm_residual_workspace", ctypes.byref(P.csr), ctypes.byref(nb))
-    ws = P._ws_cache.get(("res", nb.value))
-    if ws is None:
-        ws = torch.empty(nb.value, dtype=torch.uint8, device=P.device)
-        P._ws_cache[("res", nb.value)] = ws
+    ws = P._scratch(nb.value)
     out = torch.empty((), dtype=torch.float64, device=P.device)
     C.call("fmm_sddmm_residual", ctypes.byref(P.csr), _ptr(A), _ptr(B), r, dcode, _ptr(out), _ptr(ws), nb.value,
            _stream())
