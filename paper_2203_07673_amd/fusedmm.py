@@ -974,8 +974,9 @@ def gat_scores(H, a1, a2):
             raise ValueError(f"{name} must hold r = {r} values on {H.device}")
     s = torch.empty(n, dtype=odt, device=H.device)
     t = torch.empty(n, dtype=odt, device=H.device)
-    C.call("fmm_gat_scores", _ptr(H.contiguous()), n, r, dcode, _ptr(a1.contiguous()), _ptr(a2.contiguous()),
-           _ptr(s), _ptr(t), _stream())
+    # named: a temporary's memory would go to the next copy before the call
+    H, a1, a2 = H.contiguous(), a1.contiguous(), a2.contiguous()
+    C.call("fmm_gat_scores", _ptr(H), n, r, dcode, _ptr(a1), _ptr(a2), _ptr(s), _ptr(t), _stream())
     return s, t
 
 
@@ -1042,9 +1043,9 @@ def _gat_backward(P: Pattern, H, a1, a2, out, dO, negative_slope, softmax, want_
     da2 = torch.empty(r, dtype=odt, device=P.device)
     dS = torch.empty(max(1, P.nnz), dtype=odt, device=P.device) if want_dS else None
     ws, wb = P._gat_workspace(True, r, dcode)
-    C.call("fmm_gat_backward", ctypes.byref(P.csr), ctypes.byref(P.csc), _ptr(H), _ptr(a1.contiguous()),
-           _ptr(a2.contiguous()), _ptr(s), _ptr(t), _ptr(out), _ptr(lse if softmax else None), _ptr(dO), r, dcode,
-           float(negative_slope),
+    a1, a2 = a1.contiguous(), a2.contiguous()
+    C.call("fmm_gat_backward", ctypes.byref(P.csr), ctypes.byref(P.csc), _ptr(H), _ptr(a1), _ptr(a2), _ptr(s), _ptr(t),
+           _ptr(out), _ptr(lse if softmax else None), _ptr(dO), r, dcode, float(negative_slope),
            (C.FMM_GAT_SOFTMAX if softmax else 0) | dflag, _ptr(dH), _ptr(da1), _ptr(da2), _ptr(dS), _ptr(ws), wb,
            _stream())
     return dH, da1, da2, (dS[:P.nnz] if want_dS else None)
