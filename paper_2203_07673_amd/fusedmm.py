@@ -1036,6 +1036,8 @@ def _gat_backward(P: Pattern, H, a1, a2, out, dO, negative_slope, softmax, want_
         lse = torch.empty(P.m, dtype=odt, device=P.device)
         gat_forward(P, H, a1, a2, negative_slope, True, out=torch.empty_like(out), lse=lse)
     s, t = gat_scores(H, a1, a2) if scores is None else scores
+    for name, x in (("s", s), ("t", t)):
+        _check_buf(name, x, P.device, odt, (P.n,))
     dH = torch.empty(P.n, r, dtype=torch.bfloat16 if grad16 else odt, device=P.device)
     if grad16:
         dflag |= C.FMM_GRAD_BF16
@@ -1109,6 +1111,8 @@ class _GAT(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dO):
         H, a1, a2, out, s, t, lse = ctx.saved_tensors
+        # saved-tensor hooks may hand vectors back in another layout
+        s, t, lse = s.contiguous(), t.contiguous(), None if lse is None else lse.contiguous()
         want_dS = ctx.needs_input_grad[4]
         dH, da1, da2, dS = _gat_backward(ctx.Q, H, a1, a2, out, _upstream(dO, H, ctx.grad_bf16), ctx.slope,
                                          ctx.softmax, want_dS, lse, (s, t), _grad16(H, True))
