@@ -299,9 +299,12 @@ class Pattern:
 
     def set_line_order(self, orient, enabled: bool):
         """Process one orientation's lines by decreasing length (True) or in index order."""
-        self._orders[orient] = self._order(orient, self._long_len(orient)) if enabled else None
+        if enabled:
+            self._orders[orient] = self._order(orient, self._long_len(orient))
+            self._wait()
+        else:
+            self._orders[orient] = None
         self._order_chosen[orient] = True
-        self._wait()
         self._refresh(orient)
 
     @property

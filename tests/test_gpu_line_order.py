@@ -66,3 +66,23 @@ def test_only_the_default_order_is_left_out():
     R = _pattern(m, n)
     R.apply_tuning(t)
     assert R.tuning == t and ordered(R, 256, torch.float32)
+
+
+def test_index_order_under_capture():
+    """Going back to index order asks nothing of the GPU, so a program may do it while it
+    captures a graph."""
+    log("index order under capture")
+    P = _pattern(3000, 16, line_order=True)
+    A, B, out = torch.randn(3000, 64, device="cuda"), torch.randn(16, 64, device="cuda"), torch.empty(3000, 64, device="cuda")
+    want = F.fusedmm_a_raw(P, A, B)[0]
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        P.set_line_order(C.FMM_CSR, False)
+        F.fusedmm_a_raw(P, A, B, out=out)
+    assert P.orders["csr"] is None
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
