@@ -95,7 +95,7 @@ typedef enum fmm_orient { FMM_CSR = 0, FMM_CSC = 1 } fmm_orient;
  *
  * Optional split schedule (from fmm_schedule_count / fmm_schedule_fill): major lines
  * with more than long_len stored entries are cut into chunks that run in parallel and
- * are summed afterwards in chunk order.  n_chunks == 0 disables it.
+ * are summed afterwards in a fixed order.  n_chunks == 0 disables it.
  *
  * order: optional processing order of the major lines (from fmm_line_order), a
  * permutation of [0, major extent); NULL processes lines in index order.  It changes
@@ -497,7 +497,9 @@ fmm_status fmm_spmm_b_backward(const fmm_sparse *S_csr, const fmm_sparse *S_csc,
  *
  * The forward is one pass per row: edge values never reach memory (with the softmax the
  * running maximum and normaliser are kept with the partial sum and rescaled as the
- * maximum grows).  Rows with no stored entry give 0.  dtype is H's storage (FMM_F32,
+ * maximum grows).  Rows with no stored entry give 0; rows whose softmax has no finite
+ * normaliser (a NaN edge value, none above minus infinity) give NaN, split or not.  dtype
+ * is H's storage (FMM_F32,
  * FMM_BF16, FMM_F64); a1, a2, s, t, out and S's values are float32 (float64 for
  * FMM_F64).  A split schedule on S is honoured; it then needs a workspace of
  * fmm_gat_workspace() bytes.  Multi-head attention is one call per head.  With the

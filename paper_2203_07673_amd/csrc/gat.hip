@@ -9,7 +9,7 @@
 // The fused kernel keeps the softmax state of a row (running maximum m, normaliser l
 // and the weighted sum) in registers and rescales it when the maximum grows, so a row
 // is read once and no edge value is written to memory.  Long rows are split into
-// chunks whose (sum, m, l) triples are combined afterwards in chunk order.
+// chunks whose (sum, m, l) triples are combined afterwards in a fixed order.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
