@@ -60,7 +60,6 @@ inline bool line_vectors(const LineArgs &a, int rows, int vw)
 // elements cover r.
 Shape default_shape(int r, int vw);
 bool shape_supported(Shape s, int r, int vw);
-int max_r(int path, int r);  // 0 when r is not supported for the dtype path
 
 // The form of a pass: elements per vector and lane-group shape.  A shape given by hint that
 // covers r in vectors is taken as it is.

@@ -531,27 +531,6 @@ template <int L, int GPL> __device__ __forceinline__ double cross_group_sum(doub
     return x;
 }
 
-// Sum over the G groups (of L lanes each) that share an aligned span of L * G lanes (16, 32
-// or 64).  Each step adds the other half of a span, so every lane ends with the same bits:
-// eight lanes apart by rotation, four apart by a shift up for the even banks of four lanes
-// and a shift down for the odd ones, then the row-pair and half-wave swaps.
-template <int L, int G> __device__ __forceinline__ float line_sum(float x) {
-    constexpr int span = L * G;
-    static_assert(G == 1 || span == 16 || span == 32 || span == 64, "whole rows of 16 lanes");
-    if constexpr (G > 1) {
-        if constexpr (L <= 1) x += dpp_f<0xB1>(x);
-        if constexpr (L <= 2) x += dpp_f<0x4E>(x);
-        if constexpr (L <= 8) x += dpp_f<0x128>(x);
-        if constexpr (L <= 4) {
-            const int up = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x104, 0xF, 0x5, false);
-            x += __int_as_float(__builtin_amdgcn_update_dpp(up, __float_as_int(x), 0x114, 0xF, 0xA, false));
-        }
-        if constexpr (L <= 16 && span >= 32) x = swap16_sum(x);
-        if constexpr (L <= 32 && span >= 64) x = swap32_sum(x);
-    }
-    return x;
-}
-
 // ------------------------------------------------------------------ one line
 
 // Operands of a line pass (device pointers; types fixed by the template).

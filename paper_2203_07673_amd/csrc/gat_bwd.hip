@@ -39,12 +39,6 @@ namespace {
 template <class Acc> __device__ __forceinline__ Acc bexp(Acc x);
 template <> __device__ __forceinline__ float bexp<float>(float x) { return expf(x); }
 template <> __device__ __forceinline__ double bexp<double>(double x) { return exp(x); }
-template <class Acc> __device__ __forceinline__ Acc blog(Acc x);
-template <> __device__ __forceinline__ float blog<float>(float x) { return logf(x); }
-template <> __device__ __forceinline__ double blog<double>(double x) { return log(x); }
-template <class Acc> __device__ __forceinline__ Acc bneg_inf();
-template <> __device__ __forceinline__ float bneg_inf<float>() { return -__builtin_huge_valf(); }
-template <> __device__ __forceinline__ double bneg_inf<double>() { return -__builtin_huge_val(); }
 
 constexpr int kFinishBlocks = 2048;  // most blocks of the pass that sums da1 and da2
 
