@@ -569,7 +569,7 @@ fmm_status fmm_gat_backward(const fmm_sparse *S_csr, const fmm_sparse *S_csc, co
  * vectors with a pass over their chunks per step, followed by one kernel that forms the step
  * sizes and updates X, the residual and the direction.  A line with zero residual or
  * curvature keeps its iterate.  rhs and X: nmajor x r float32; F: minor x r, dtype FMM_F32 or FMM_BF16;
- * work: fmm_cg_work_size() bytes (three nmajor x r float32 blocks and nmajor scalars);
+ * work: fmm_cg_work_size() bytes (two nmajor x r float32 blocks and nmajor scalars);
  * ws: split partials of S as for the fused calls.  lambda >= 0.
  */
 fmm_status fmm_cg_work_size(int32_t nmajor, int32_t r, size_t *bytes);

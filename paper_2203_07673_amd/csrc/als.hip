@@ -675,7 +675,7 @@ fmm_status solve_lines(const fmm_sparse *S, const void *F, int32_t r, int32_t dt
         c.R = work;
         c.P = work + (size_t)n * r;
         c.partial = static_cast<const float *>(ws);
-        c.rr = work + 3 * (size_t)n * r;
+        c.rr = work + 2 * (size_t)n * r;
         c.rhs = rhs ? rhs : c.R;
         auto partials = [&](const float *H) {  // of <H_line, F_j> F_j, or for NULL of val_p F_j
             return by_row(dtype, r, [&](auto tf, auto L, auto NV, auto VW, auto RAG) {
@@ -718,7 +718,7 @@ fmm_status fmm_cg_work_size(int32_t nmajor, int32_t r, size_t *bytes)
 {
     if (!bytes) return FMM_ERR_NULL;
     if (nmajor < 0 || r < 1) return FMM_ERR_DIM;
-    *bytes = (3 * (size_t)nmajor * r + (size_t)nmajor) * sizeof(float);
+    *bytes = (2 * (size_t)nmajor * r + (size_t)nmajor) * sizeof(float);  // residual and direction of split lines, <R, R>
     return FMM_OK;
 }
 
