@@ -19,11 +19,12 @@ namespace fmm {
 // lines have few chunks.  2^17 lines of two chunks, the forward without / with: r = 8 279 / 239 us,
 // r = 16 276 / 238, r = 64 667 / 640; attention step on 2^16 of them, r = 8 444 / 365.  R-MAT of 64
 // per row at 2^17 (9400 lines of 4.8 chunks, r = 64, 2350 waves) 153 / 157; 2^20, 16 per row
-// (21700 lines of 4.1, 5400 waves) 517 / 516.
+// (21700 lines of 4.1, 5400 waves) 517 / 516.  Two groups a wave gain nothing: layered calls on
+// 2^17, r = 100 (3200 lines of 3.3, 1600 waves) 667 / 673.
 inline bool pack_merges(int32_t n_splits, int32_t n_chunks, int groups)
 {
     const int64_t waves = n_splits / groups;
-    return groups > 1 && (waves >= 4096 || (waves >= 1024 && n_chunks < 4 * (int64_t)n_splits));
+    return groups > 2 && (waves >= 4096 || (waves >= 1024 && n_chunks < 4 * (int64_t)n_splits));
 }
 
 constexpr int32_t kMergeAlone = 32;
