@@ -44,10 +44,20 @@ inline bool vector_rows(int r, int vw) { return r % vw == 0 || r * (16 / vw) > 6
 //   no rule needed  dS with its gradient, 300k: r = 17 398 / 250, 31 410 / 326; SDDMM 268 / 240
 //                  and 313 / 320
 // Wider rows of a two-row pass lie within 2% either way.  float64 stays in vectors.
+//
+// Small patterns with split lines go by elements up to 64 of them: there the longest chains
+// decide, and a chunk goes faster with 32 or 64 lanes than with the 8 or 16 of the vectors, while
+// the chip has waves to spare.  The line lies at entries times lanes.  R-MAT, 2^13 lines, 8 per
+// row: r = 54 one row 20 / 24, two rows 30 / 38, r = 17 19 / 23 and 27 / 36; one row at 2^24: 2^15
+// lines, 8 per row, r = 54 28 / 32, 2^16, r = 23 28 / 34; at 2^25: 2^16, 8 per row, r = 54 41 / 36,
+// 2^17, r = 23 39 / 39; two rows at 2^25: 53 / 57 and 50 / 61 (weights by permutation 42 / 45 and
+// 43 / 51), at 2^26 98 / 73 and (2^17, 16 per row, r = 17) 79 / 73.
 inline bool line_vectors(const LineArgs &a, int rows, int vw)
 {
     const int r = a.r;
     if (r % vw == 0 || vw != 4 || r <= 16) return vector_rows(r, vw);
+    if (a.n_chunks > 0 && r <= 64)
+        return (double)a.nnz * (r > 32 ? 64 : 32) > (rows == 2 || a.wperm ? 1 << 25 : 1 << 24);
     if (rows == 0 || a.n_chunks > 0 || r > 32 * rows) return true;
     const double mb = 1e-6 * rows * 4 * r * a.nminor;  // of gathered matrices
     const bool short_lines = (double)a.nnz < 12.0 * a.nlines;

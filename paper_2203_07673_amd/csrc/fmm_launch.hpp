@@ -74,7 +74,7 @@ hipError_t launch_one(const LineArgs &a, hipStream_t stream)
 template <int OP, class TH, class TG1, class TG2, class Acc, int L, int NV, int VW, int U>
 hipError_t launch_kind(const LineArgs &a, hipStream_t stream)
 {
-    if constexpr (has_wave_kernel<Acc, L>() && !(VW == 1 && L == 32))  // without split lines (line_vectors)
+    if constexpr (has_wave_kernel<Acc, L>() && !(VW == 1 && L == 32))  // small patterns, where groups are faster
         if (chunks_by_waves<OP, L, U>(a)) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, true>(a, stream);
     if constexpr (has_hints(L))
         if (a.hot) return launch_one<OP, TH, TG1, TG2, Acc, L, NV, VW, U, false, true>(a, stream);
@@ -96,10 +96,11 @@ hipError_t launch_shape(const LineArgs &a, Shape shape, hipStream_t stream)
     FMM_SHAPE_CASE(4, 1)
     FMM_SHAPE_CASE(8, 1)
     FMM_SHAPE_CASE(16, 1)
-    // one element per lane: up to 16 of them, in float32 up to 32 or 64 (line_vectors)
-    constexpr bool two = sizeof(Acc) == 4 && two_row<OP>(), one = sizeof(Acc) == 4 && (OP == OP_FUSED1 || OP == OP_SPMM1);
-    if constexpr (VW > 1 || one || two) { FMM_SHAPE_CASE(32, 1) }
-    if constexpr (VW > 1 || two) { FMM_SHAPE_CASE(64, 1) }
+    // one element per lane: up to 16 of them, in float32 up to 64 (line_vectors)
+    if constexpr (VW > 1 || sizeof(Acc) == 4) {
+        FMM_SHAPE_CASE(32, 1)
+        FMM_SHAPE_CASE(64, 1)
+    }
     if constexpr (VW > 1) {
         FMM_SHAPE_CASE(16, 2)
         FMM_SHAPE_CASE(32, 2)

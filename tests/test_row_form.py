@@ -40,10 +40,22 @@ def _form(r, lines, minor, mean, two_row, dtype=C.FMM_F32, n_chunks=0):
     (True, 75, 300000, 30, 32, 4), (True, 60, 300000, 30, 16, 4)])
 def test_row_form(two_row, r, lines, mean, lanes, vw):
     assert _form(r, lines, lines, mean, two_row) == (lanes, vw)
-    # a power-law pattern has split lines: in vectors
-    assert _form(r, lines, lines, mean, two_row, n_chunks=100)[1] == (1 if r <= 16 else 4)
+    # a power-law pattern has split lines: in vectors, a small one by elements
+    small = r <= 64 and lines * mean * (64 if r > 32 else 32) <= (1 << 25 if two_row else 1 << 24) and r % 4
+    assert _form(r, lines, lines, mean, two_row, n_chunks=100)[1] == (1 if r <= 16 or small else 4)
     # nothing but float32 goes by elements above 16 of them
     assert _form(r, lines, lines, mean, two_row, C.FMM_F64)[1] == 2
+
+
+@pytest.mark.parametrize("two_row", [False, True])
+@pytest.mark.parametrize("r,lanes", [(17, 32), (31, 32), (33, 64), (63, 64)])
+def test_row_form_of_small_split_patterns(two_row, r, lanes):
+    """Split lines: by elements while entries times lanes stay below 2^24 (one row), 2^25 (two)."""
+    limit = (1 << 25 if two_row else 1 << 24) // lanes // 8  # lines of 8 entries
+    assert _form(r, limit, 1000, 8, two_row, n_chunks=3) == (lanes, 1)
+    assert _form(r, limit + 1, 1000, 8, two_row, n_chunks=3) == (8 if r <= 32 else 16, 4)
+    assert _form(r, 100, 1000, 8, two_row, C.FMM_F64, n_chunks=3)[1] == 2
+    assert _form(r + 64, 100, 1000, 8, two_row, n_chunks=3)[1] == 4
 
 
 def test_given_shape_is_taken():
@@ -102,3 +114,56 @@ def test_rows_by_elements(r):
         gate("dA'", host(gA), b[0], b[2], TOL_F32)
     P.set_gather_hints(C.FMM_CSR, 5)
     assert torch.equal(F.fusedmm_b_backward_raw(P, Ad, Bd, Gbd)[0], F.fusedmm_b_backward_raw(F.Pattern.from_csr(S), Ad, Bd, Gbd)[0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("long_len", [128, 16])
+@pytest.mark.parametrize("r", [17, 31, 33, 63])
+def test_split_lines_by_elements(r, long_len):
+    """A small pattern with split lines, whose passes go by elements: every operation in both
+    orientations against the oracle, on bases aligned to one element."""
+    log(f"split lines by elements r={r} long_len={long_len}")
+    m, n = 260, 700
+    rng = np.random.default_rng(41)
+    lens = rng.integers(0, 12, m)
+    lens[0], lens[5], lens[6], lens[259] = 700, 129, 128, 300
+    cols = [np.sort(rng.choice(n, k, replace=False)) for k in lens]
+    for i in range(20, 220):  # and one long column
+        if 3 not in cols[i]:
+            cols[i] = np.sort(np.append(cols[i], 3))
+    rowptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    S = CsrPattern(m, n, rowptr, np.concatenate(cols).astype(np.int32), rng.random(rowptr[-1]).astype(np.float32))
+    P = F.Pattern.from_csr(S, long_len=long_len, chunk=long_len)
+    for orient in (C.FMM_CSR, C.FMM_CSC):
+        assert P.splits["csr" if orient == C.FMM_CSR else "csc"] == long_len
+        for two_row in (False, True):
+            assert P.launch_shape(orient, two_row, r, C.FMM_F32)[2] == 1
+    A, B = dense_normal(m, r, 42), dense_normal(n, r, 43)
+    G, Gb = dense_normal(m, r, 44), dense_normal(n, r, 45)
+
+    def shifted(x):
+        big = torch.zeros(x.size + 1, device="cuda")
+        big[1:] = dev(x.reshape(-1))
+        return big[1:].view(*x.shape)
+
+    Ad, Bd, Gd, Gbd = shifted(A), shifted(B), shifted(G), shifted(Gb)
+    ref, mag = ref_sddmm(S, A, B)
+    gate("R", host(F.sddmm_raw(P, Ad, Bd)), ref, mag, TOL_F32)
+    ref, mag = ref_fusedmm_a(S, A, B)
+    a = ref_fusedmm_a_backward(S, A, B, G)
+    b = ref_fusedmm_b_backward(S, A, B, Gb)
+    for fused in (True, False):
+        out, R = F.fusedmm_a_raw(P, Ad, Bd, fused=fused)
+        gate("C", host(out), ref, mag, TOL_F32)
+        gA, gB = F.fusedmm_a_backward_raw(P, Ad, Bd, Gd, fused=fused, R_ws=R)
+        gate("dA", host(gA), a[0], a[2], TOL_F32)
+        gate("dB", host(gB), a[1], a[3], TOL_F32)
+        R = None if fused else F.fusedmm_b_raw(P, Ad, Bd, fused=False)[1]
+        gA, gB = F.fusedmm_b_backward_raw(P, Ad, Bd, Gbd, fused=fused, R_ws=R)
+        gate("dA'", host(gA), b[0], b[2], TOL_F32)
+        gate("dB'", host(gB), b[1], b[3], TOL_F32)
+    dS, gA = F.fusedmm_a_backward_values_raw(P, Ad, Bd, Gd, want_dA=True)
+    gate("dA", host(gA), a[0], a[2], TOL_F32)
+    Sa = oracle.absolute(S)
+    gate("dS", host(dS), oracle.fusedmm_a_backward_values(S, A, B, G),
+         oracle.fusedmm_a_backward_values(Sa, np.abs(A), np.abs(B), np.abs(G)), TOL_F32)
