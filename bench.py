@@ -73,14 +73,25 @@ def gat_forward_bytes(n, nnz, r, e):
 
 
 def gat_backward_bytes(n, nnz, r, e):
-    """Gather-model bytes of one attention head's adjoint: the row pass (held dO_i and
-    out_i, per entry colidx + value, t_j and a gathered H_j, dS written) writes D_i and the
-    packed row scalars; the column pass (held H_j, per entry rowidx + value, the packed row
-    scalars and a gathered dO_i) writes dt_j and dH_j; the da pass reads H, ds and dt."""
+    """Gather-model bytes of one attention head's adjoint with two gathering passes: the row
+    pass (held dO_i and out_i, per entry colidx + value, t_j and a gathered H_j, dS written)
+    writes D_i and the packed row scalars; the column pass (held H_j, per entry rowidx + value,
+    the packed row scalars and a gathered dO_i) writes dt_j and dH_j; the da pass reads H, ds
+    and dt."""
     rows = 4 * (n + 1) + n * (8 * r + 8) + nnz * (8 + 4 + e * r + 4) + n * (4 + 12)
     cols = 4 * (n + 1) + n * (e * r + 4 * r + 4) + nnz * (8 + 12 + 4 * r)
     da = n * (e * r + 8)
     return rows + cols + da
+
+
+def gat_backward_once_bytes(n, nnz, r, e):
+    """The same where the column pass alone gathers (wide rows, as this bench's): D_i from dO_i
+    and out_i, packed with s_i and lse_i; the column pass as above, which also reads perm and
+    writes each entry's dx; the last pass, which sums dx by rows, reads H and updates dH."""
+    dots = n * (8 * r + 8 + 16)
+    cols = 4 * (n + 1) + n * (e * r + 4 * r + 8) + nnz * (8 + 4 + 16 + 4 * r + 4)
+    last = 4 * (n + 1) + 4 * nnz + n * (e * r + 8 * r + 4)
+    return dots + cols + last
 
 
 def als_sweep_bytes(m, n, nnz, r, cg_steps=10):
@@ -246,6 +257,8 @@ BATCH_SRC_GLOBS = SRC_GLOBS + ("paper_2203_07673_amd/csrc/batch*.hip", "paper_22
 
 
 def source_globs(workload_name):
+    if workload_name in APP_SRC_GLOBS:
+        return APP_SRC_GLOBS[workload_name]
     return BATCH_SRC_GLOBS if workload_name.startswith("batch") else SRC_GLOBS
 
 
@@ -277,6 +290,8 @@ def _csv_rows(d, suffix):
 def _short_kernel(name):
     if "line_kernel<" in name:
         return "line_kernel<" + name.split("line_kernel<", 1)[1].split(">", 1)[0] + ">"
+    if "line_wave_kernel<" in name:  # the same passes, a chunk of a split line by a whole wave
+        return "line_kernel<" + name.split("line_wave_kernel<", 1)[1].split(">", 1)[0] + ", wave>"
     return name[:120]
 
 
@@ -354,6 +369,10 @@ def _role(key):
         return "batched persistent, XCD queues (all passes of every graph)"
     if "f32_to_bf16" in key:
         return ROUNDING
+    if "cg_resident_kernel<" in key:
+        return "ALS: whole CG solve of a line"
+    if "gat_" in key:
+        return "attention head"
     return None
 
 
@@ -684,7 +703,7 @@ def run_batch(args):
     waves = 64 // info["lanes"]  # line groups sharing a wavefront in the wavefront-per-line schedule
     kname = "batch_queue_kernel" if info["xcd_aware"] == 2 else "batch_kernel"
     kernel_key = (f"void fmm::{kname}<unsigned short, float, {info['lanes']}, 8, "
-                  f"{waves if info['row_schedule'] else 1}, {waves if info['col_schedule'] else 1}>")
+                  f"{waves if info['row_schedule'] else 1}, {waves if info['col_schedule'] else 1}, true>")
     traffic = None
     f = os.path.join(ROOT, "profiles", "traffic_batch256_r64.json")
     if os.path.exists(f):
@@ -865,7 +884,7 @@ def run_gat(args):
     tb16g = timeit(lambda: step_bwd_do16(H16), args.steps, args.warmup)
     nnz, n = S.nnz, S.n
     bytes32 = heads * gat_forward_bytes(n, nnz, r, 4)
-    bbytes32 = heads * gat_backward_bytes(n, nnz, r, 4)
+    bbytes32 = heads * gat_backward_once_bytes(n, nnz, r, 4)
 
     def roofline(nbytes, t, what, region):
         achieved = nbytes / t / 1e9
@@ -883,7 +902,7 @@ def run_gat(args):
            "train_step_f32_ms": round((t32 + tb32) * 1e3, 4),
            "roofline": roofline(bytes32, t32, "fused forward of every head, fp32 (scores, line pass, merges)",
                                 "fwd_f32"),
-           "roofline_backward": roofline(bbytes32, tb32, "adjoint of every head, fp32 (row, column, da passes)",
+           "roofline_backward": roofline(bbytes32, tb32, "adjoint of every head, fp32 (D_i, column and last passes)",
                                          "bwd_f32"),
            "tuning": tuning}
     print(json.dumps(out), flush=True)
@@ -891,9 +910,9 @@ def run_gat(args):
 
 def run_als(args):
     """ALS application (Section VI-E): one sweep = 10 batched CG steps for A, then 10 for
-    B (the paper's 20 CG iterations), each step's query vectors from one FusedMM-shaped
-    pass; observations are a noisy rank-128 product on an ER pattern (2^20 x 2^20, 32 per
-    row)."""
+    B (the paper's 20 CG iterations), each line's solve in one kernel with its gathered rows
+    in registers; observations are a noisy rank-128 product on an ER pattern (2^20 x 2^20,
+    32 per row)."""
     import torch
 
     import paper_2203_07673_amd as F
@@ -1340,16 +1359,15 @@ def main():
     step_bytes = sum(kernel_bytes(k, m, n, nnz, r, e) for k in kinds)
     # exact instantiation of the dominant kernel, to look up its counter data
     from paper_2203_07673_amd import _capi as CA
-    orient = CA.FMM_CSC if dom == "bwd_col" else CA.FMM_CSR
-    L, NV, VW, U = P.launch_shape(orient, dom == "bwd_col", r, CA.FMM_F32)
-    op = 4 if dom == "bwd_col" else 3
-    kernel_key = f"line_kernel<{op}, float, float, float, float, {L}, {NV}, {VW}, {U}>"
-    traffic = load_traffic(args.workload, kernel_key)
-
     def pass_key(kind):
         o = CA.FMM_CSC if kind == "bwd_col" else CA.FMM_CSR
         Lk, NVk, VWk, Uk = P.launch_shape(o, kind == "bwd_col", r, CA.FMM_F32)
-        return f"line_kernel<{4 if kind == 'bwd_col' else 3}, float, float, float, float, {Lk}, {NVk}, {VWk}, {Uk}>"
+        shape = f"{4 if kind == 'bwd_col' else 3}, float, float, float, float, {Lk}, {NVk}, {VWk}, {Uk}"
+        hints = Lk == 64 and tuning["csc" if kind == "bwd_col" else "csr"].get("gather_hints")
+        keys = (f"line_kernel<{shape}, {'true' if hints else 'false'}>", f"line_kernel<{shape}, wave>")
+        return keys[1] if load_traffic(args.workload, keys[1]) is not None else keys[0]
+    kernel_key = pass_key(dom)
+    traffic = load_traffic(args.workload, kernel_key)
     # counter-measured bytes of the whole step (the three passes' instantiations), when
     # the committed counter summary covers them
     pass_traffic = [load_traffic(args.workload, pass_key(k)) for k in kinds]
