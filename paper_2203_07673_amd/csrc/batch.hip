@@ -246,6 +246,11 @@ fmm_status apply_schedule(fmm_batch_plan *p, int32_t tile_nnz, int32_t placement
     int per_cu = 0;
     BTRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, 0));
     if (per_cu < 1) per_cu = 1;
+    // Row-block rows with a wave per line in the column pass take the 5 that they are built for:
+    // in float32 6 fit, whose gathers crowd each other out of L2.  4 graphs of 3 to 18 thousand
+    // lines, 1.2 million entries, r = 88, tiles of 1536, 6 / 5: queues 279 / 248 us, global 226 /
+    // 210 (tiles of 2560 383 / 312).
+    if (!rw && cw && per_cu > 5) per_cu = 5;
     const int32_t n_wg = p->num_cu * per_cu;
     std::vector<std::vector<TileCost>> per_graph;
     cut_tiles(p, tile_nnz, &per_graph);

@@ -53,3 +53,15 @@ def test_row_passes_by_size(r, dtype, dc, entries):
         c = F.fusedmm_a_raw(P, A[k], B[k])[0]
         dA, dB = F.fusedmm_a_backward_raw(P, A[k], B[k], G[k])
         assert torch.equal(both.C[k], c) and torch.equal(both.dA[k], dA) and torch.equal(both.dB[k], dB)
+
+
+def test_workgroups_of_mixed_schedule():
+    """Row-block rows with a wave per line in the column pass: no more than 5 workgroups a CU,
+    for which the kernels are built."""
+    P = _pattern(4000, 3000, 1 << 17, 911)
+    r = 88
+    plan = F.BatchPlan([P], [dev(dense_normal(4000, r, 1))], [dev(dense_normal(3000, r, 2))],
+                       [dev(dense_normal(4000, r, 3))])
+    for placement in (plan.PLACE_GLOBAL, plan.PLACE_XCD, plan.PLACE_QUEUES):
+        plan.set_schedule(1536, placement, False, True)
+        assert plan.info()["n_workgroups"] <= 5 * F.device_info()["num_cu"]
